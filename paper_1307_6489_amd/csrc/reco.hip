@@ -14,16 +14,28 @@
 //                   cameras track the raw high-gain maximum with packed
 //                   16-bit max and re-stream the low gain only for lanes that
 //                   own a switched pixel.  D and the threshold flags go to LDS.
-//   2. mask         neighbour flags gathered from LDS, one ballot per
-//                   64-pixel word.
-//   3. compaction   popcount prefix over the mask words gives every cleaned
-//                   pixel a slot; q, x, y and the peak time (window samples
-//                   re-read for cleaned pixels only) are stored per slot.
-//   4. islands      lock-free union-find over the slots in LDS.
-//   5. Hillas       four block reductions (cog, centred second moments,
-//                   longitudinal moments + time sums, time-gradient sums),
-//                   each a fixed-order wavefront butterfly + wave-ordered sum,
-//                   so results are deterministic.
+//   2. mask         only pixels at or above a threshold can be mask pixels;
+//                   each wavefront keeps a run of its flagged ones and decides
+//                   them by their neighbours' flags in LDS.
+//   3. slots        popcount prefix over the mask words gives every cleaned
+//                   pixel a slot (pixel order); the peak time comes from a
+//                   re-read of its window samples.
+//   4. islands      images of up to 64 mask pixels: flood fill over slot
+//                   masks by one wavefront; larger ones: lock-free union-find
+//                   over the slots in LDS.
+//   5. Hillas       three reductions (cog, centred second moments,
+//                   longitudinal moments + time sums), each a fixed-order
+//                   wavefront butterfly + wave-ordered sum, so results are
+//                   deterministic.
+//
+// Where the trace read is short (the fixed window: 16 KB of a 2048-pixel
+// event) a telescope is one serial chain of some ten microseconds, bound by
+// the latencies of steps 2 to 5, and the rate is the telescopes in flight
+// over that chain.  Both were worked on together: the chain after the
+// extraction went from 11 to 5 us, the LDS of a telescope from 32.3 to 16.8
+// KB and the fixed window's registers from 72 to 62 (eight workgroups per
+// compute unit, five before).  8000 camera events of the 1:3:6 mix: fixed
+// window 134 -> 61 us.
 #include <cfloat>
 #include <cmath>
 
@@ -541,13 +553,44 @@ __device__ __forceinline__ uint32_t wave_sum_u32_last(uint32_t v) {
   return v;
 }
 
+// Sums over the wavefront of eight values at once.  On return lane 16 r
+// holds the totals of v[2 r] and v[2 r + 1] (r = 0..3): two lane swaps fold
+// the halves and then the rows together while they halve the number of
+// registers (a swap of two registers leaves one value's partners in the
+// lower lanes and the other's in the upper ones), and the rows of 16 end
+// with rotations.  About 20 instructions, against 48 for eight separate
+// sums.
+__device__ __forceinline__ u32x2 wave_sum8(const uint32_t (&v)[8]) {
+  uint32_t u[4], w[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v[k], v[k + 4], false, false);
+    u[k] = r[0] + r[1];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(u[k], u[k + 2], false, false);
+    w[k] = r[0] + r[1];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    w[k] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[k], 0x128, 0xF, 0xF, false);  // row_ror:8
+    w[k] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[k], 0x124, 0xF, 0xF, false);  // row_ror:4
+    w[k] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[k], 0x122, 0xF, 0xF, false);  // row_ror:2
+    w[k] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[k], 0x121, 0xF, 0xF, false);  // row_ror:1
+  }
+  return u32x2{w[0], w[1]};
+}
+
 // Global peak, first stage for one group: the wave's sum of the raw
 // high-gain samples of pixels below N, slice by slice, added into rows[k]
 // (stored on the first pass); returns the group's low-gain bits (full-trace
-// raw high-gain maximum >= switch).
+// raw high-gain maximum >= switch).  Slices stream in chunks of eight,
+// double buffered, and a chunk's eight sums are reduced together.
 template <int PPL, int CH>
 __device__ __forceinline__ uint32_t global_rows_group(const DevCam& c, __amdgpu_buffer_rsrc_t r, int pix0, int np,
                                                       int T, bool dual, uint32_t* rows, bool first) {
+  static_assert(CH % 8 == 0, "slices are summed eight at a time");
   constexpr int ND = PPL / 2;
   const uint32_t voff = (uint32_t)pix0 * 2u, stride = (uint32_t)np * 2u;
   const int nv = min(max(c.n_pix - pix0, 0), PPL);
@@ -557,23 +600,42 @@ __device__ __forceinline__ uint32_t global_rows_group(const DevCam& c, __amdgpu_
     msk[h] = (2 * h + 1 < nv) ? 0xffffffffu : (2 * h < nv ? 0x0000ffffu : 0u);
     rmax[h] = 0;
   }
-  const bool writer = (threadIdx.x & (kWave - 1)) == kWave - 1;
-  uint32_t A[CH][ND];
-  for (int k0 = 0; k0 < T; k0 += CH) {
-    load_chunk<PPL, CH>(A, r, voff, 0u, stride, k0);
+  const int lane = threadIdx.x & (kWave - 1);
+  const us2 ones = {1, 1};
+  auto reduce = [&](const uint32_t (&A)[CH][ND], int k0) {
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      if (k0 + j >= T) continue;
-      uint32_t v = 0;
+    for (int j0 = 0; j0 < CH; j0 += 8) {
+      if (k0 + j0 >= T) continue;
+      uint32_t v[8];
 #pragma unroll
-      for (int h = 0; h < ND; ++h) {
-        const uint32_t x = A[j][h] & msk[h];
-        v += lo16(x) + hi16(x);
-        rmax[h] = pkmax16(rmax[h], x);
+      for (int j = 0; j < 8; ++j) {
+        // slices past the trace are summed too (their totals are never
+        // read) but must not enter the maximum
+        const uint32_t keep = k0 + j0 + j < T ? 0xffffffffu : 0u;
+        v[j] = 0;
+#pragma unroll
+        for (int h = 0; h < ND; ++h) {
+          const uint32_t x = A[j0 + j][h] & msk[h];
+          v[j] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, x), ones, v[j], false);
+          rmax[h] = pkmax16(rmax[h], x & keep);
+        }
       }
-      v = wave_sum_u32_last(v);
-      if (writer) rows[k0 + j] = first ? v : rows[k0 + j] + v;
+      const u32x2 t = wave_sum8(v);
+      if ((lane & 15) == 0) {
+        uint32_t* dst = rows + k0 + j0 + (lane >> 3);
+        dst[0] = first ? t[0] : dst[0] + t[0];
+        dst[1] = first ? t[1] : dst[1] + t[1];
+      }
     }
+  };
+  uint32_t A[CH][ND], B[CH][ND];
+  load_chunk<PPL, CH>(A, r, voff, 0u, stride, 0);
+  for (int k0 = 0; k0 < T; k0 += 2 * CH) {
+    if (k0 + CH < T) load_chunk<PPL, CH>(B, r, voff, 0u, stride, k0 + CH);
+    reduce(A, k0);
+    if (k0 + CH >= T) break;
+    if (k0 + 2 * CH < T) load_chunk<PPL, CH>(A, r, voff, 0u, stride, k0 + 2 * CH);
+    reduce(B, k0 + CH);
   }
   uint32_t sw = 0;
   if (dual) {
@@ -921,8 +983,19 @@ __device__ __forceinline__ uint32_t pixel_flag_at(const DevCam& c, int g, int i,
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup-shared state of one camera event.
+// Workgroup-shared state of one camera event: 16.4 KB, so that LDS lets nine
+// 256-thread workgroups share a compute unit (it was 32.3 KB, five, while
+// every mask pixel had its packed charge and time here; the fixed window,
+// bound by how many telescopes are in flight, runs by it).
 // ---------------------------------------------------------------------------
+// One mask pixel of a small image, as the lane that found it leaves it for
+// wavefront 0.
+struct SmallSlot {
+  int32_t d, nt;   // D and Nt of its window
+  float a, x, y;   // ADC per p.e., position
+  uint32_t s;      // window start | border << 8
+};
+
 struct TelSmem {
   union {
     uint32_t key[kMaxPix];   // (S << 8) | (255 - s*) per pixel; reused as union-find parents
@@ -930,49 +1003,81 @@ struct TelSmem {
   };
   uint8_t flag[kMaxPix];     // bit 0: D >= Tb, bit 1: D >= Tp, bit 2: low gain
   uint64_t mbits[kMaxWords]; // cleaning mask, one word per 64 pixels
-  int32_t wbase[kMaxWords + 1];
-  uint16_t list[kMaxPix];    // slot -> pixel | gain << 15
-  union alignas(16) {        // 16-byte aligned: slices are staged with 16-byte stores
-    struct {
-      // per slot, fused path: D and Nt in their low 28 bits (both fit in 28
-      // signed bits), s* split over the top 4 bits of each; unfused path:
-      // D in dq, the float bits of the given peak time in nt
-      uint32_t dq[kMaxPix];
-      uint32_t nt[kMaxPix];
-    } slot;
-    uint16_t xrow[kNbrRows * (kMaxPix + 8)];  // neighbour peak: staged slices + zero slot (extraction only)
-  };
-  double red[16 * 8];        // cross-wave reduction scratch
+  int32_t wbase[kMaxWords];  // slot of each word's first mask pixel
   int32_t nlow_w[16];        // per-wave counts of low-gain pixels
   int32_t start;             // global peak window start
+  // from here on the neighbour peak's staged slices overlay the rest (extraction only)
+  alignas(16) uint16_t list[kMaxPix];  // flagged pixels, a run per wavefront; then slot -> pixel (large images)
+  union {
+    struct {
+      SmallSlot slot[kWave];
+      unsigned long long adj[kWave];  // slots adjacent to each slot
+    } small;
+    double red[16 * 8];      // cross-wave reduction scratch (large images)
+  };
 };
 
-__device__ __forceinline__ int32_t sext28(uint32_t v) { return (int32_t)(v << 4) >> 4; }
+constexpr size_t kXrowBytes = sizeof(uint16_t) * kNbrRows * (kMaxPix + 8);
+template <int EX>
+constexpr size_t smem_bytes() {
+  return EX == kExNeighbour ? (offsetof(TelSmem, list) + kXrowBytes + 15) & ~size_t(15) : sizeof(TelSmem);
+}
 
-// Charge of slot j: q = D / (256 a), formed where it is used (the same float
-// every time, and the float the calibration writes as q); on the unfused
-// path the given q.
-template <bool FUSED>
-__device__ __forceinline__ float slot_q(const DevCam& c, const TelSmem& sm, int j, int i) {
-  if constexpr (FUSED) {
-    const int g = sm.list[j] >> 15;
-    return (float)sext28(sm.slot.dq[j]) / (256.0f * c.a[g * c.n_pix_pad + i]);
+// Butterfly sum of a 32-bit or 64-bit value over the wavefront: every lane
+// gets the sum over the pairing tree (i, i ^ 32), (i, i ^ 16), ... (i, i ^ 1).
+// The exchanges are register moves, none through LDS: the halves and rows
+// by the lane swaps (a swap of a register with its copy leaves the two
+// partners of every lane in the two results), then within a row of 16 a
+// rotation by 8, a rotation by 4 (the values already agree under i ^ 8, so
+// lane i + 4 holds what lane i ^ 4 does) and quad permutes.  A dependent
+// step costs a few cycles where an LDS permute costs over a hundred; the
+// three reductions of an image went from 1.4 us to 0.3 us.
+template <int STEP>
+__device__ __forceinline__ void partner_u32(uint32_t v, uint32_t* a, uint32_t* b) {
+  if constexpr (STEP == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    *a = r[0];
+    *b = r[1];
+  } else if constexpr (STEP == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    *a = r[0];
+    *b = r[1];
   } else {
-    return __uint_as_float(sm.slot.dq[j]);
+    constexpr int ctrl = STEP == 8 ? 0x128 : STEP == 4 ? 0x124 : STEP == 2 ? 0x4E : 0xB1;
+    *a = v;
+    *b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, false);
   }
 }
 
-// Peak time of slot j (samples): s* + Nt / D from the packed slot, or the
-// given float time on the unfused path.
-template <bool FUSED, int W>
-__device__ __forceinline__ double slot_t(const TelSmem& sm, int j) {
-  const uint32_t a = sm.slot.dq[j], b = sm.slot.nt[j];
-  if constexpr (FUSED) {
-    const int s = (int)(((a >> 28) << 4) | (b >> 28));
-    return peak_time<W>(s, sext28(b), sext28(a));
+template <int STEP, typename T>
+__device__ __forceinline__ T butterfly_step(T v) {
+  if constexpr (sizeof(T) == 4) {
+    uint32_t a, b;
+    partner_u32<STEP>(__builtin_bit_cast(uint32_t, v), &a, &b);
+    return __builtin_bit_cast(T, a) + __builtin_bit_cast(T, b);
   } else {
-    return (double)__uint_as_float(b);
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    uint32_t al, bl, ah, bh;
+    partner_u32<STEP>((uint32_t)u, &al, &bl);
+    partner_u32<STEP>((uint32_t)(u >> 32), &ah, &bh);
+    return __builtin_bit_cast(T, ((uint64_t)ah << 32) | al) + __builtin_bit_cast(T, ((uint64_t)bh << 32) | bl);
   }
+}
+
+template <typename T, int NV>
+__device__ __forceinline__ void butterfly(T (&v)[NV]) {
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = butterfly_step<32>(v[k]);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = butterfly_step<16>(v[k]);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = butterfly_step<8>(v[k]);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = butterfly_step<4>(v[k]);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = butterfly_step<2>(v[k]);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = butterfly_step<1>(v[k]);
 }
 
 template <typename T, int NV, int NT>
@@ -980,11 +1085,7 @@ __device__ __forceinline__ void block_sum(T (&v)[NV], double* red_raw) {
   T* red = reinterpret_cast<T*>(red_raw);
   constexpr int NW = NT / kWave;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off, kWave);
-  }
+  butterfly(v);
   if (lane == 0) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) red[wave * NV + k] = v[k];
@@ -1004,23 +1105,12 @@ __device__ __forceinline__ void block_sum(T (&v)[NV], double* red_raw) {
 // butterfly of block_sum, then its cross-wave sum, here 0 + the wave's sum.
 template <typename T, int NV>
 __device__ __forceinline__ void wave_sum(T (&v)[NV]) {
+  butterfly(v);
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off, kWave);
-    v[k] = T(0) + v[k];
-  }
+  for (int k = 0; k < NV; ++k) v[k] = T(0) + v[k];
 }
 
-// Workgroup total of a per-thread count: each wavefront's sum goes to
-// sm.nlow_w before a barrier the caller provides; total_count reads them
-// after it.
-__device__ __forceinline__ void post_count(TelSmem& sm, int v) {
-#pragma unroll
-  for (int off = kWave / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-  if ((threadIdx.x & (kWave - 1)) == 0) sm.nlow_w[threadIdx.x / kWave] = v;
-}
-
+// Workgroup total of the wavefronts' low-gain counts (sm.nlow_w, behind a barrier).
 template <int NT>
 __device__ __forceinline__ int total_count(const TelSmem& sm) {
   int s = 0;
@@ -1031,120 +1121,220 @@ __device__ __forceinline__ int total_count(const TelSmem& sm) {
 
 __device__ __forceinline__ bool mask_bit(const TelSmem& sm, int i) { return (sm.mbits[i >> 6] >> (i & 63)) & 1ull; }
 
+// Slot of mask pixel i (after scan_phase).
 __device__ __forceinline__ int mask_slot(const TelSmem& sm, int i) {
   const uint64_t w = sm.mbits[i >> 6];
   return sm.wbase[i >> 6] + __popcll(w & ((1ull << (i & 63)) - 1ull));
 }
 
-// Phase 1 (fused): extraction of all pixels into LDS.  Returns this thread's
-// count of low-gain pixels.
+template <int PPL>
+__device__ __forceinline__ void store_keys(uint32_t* dst, const uint32_t (&key)[PPL]) {
+  if constexpr (PPL == 2) {
+    *reinterpret_cast<u32x2*>(dst) = u32x2{key[0], key[1]};
+  } else {
+#pragma unroll
+    for (int p = 0; p < PPL; p += 4)
+      *reinterpret_cast<u32x4*>(dst + p) = u32x4{key[p], key[p + 1], key[p + 2], key[p + 3]};
+  }
+}
+
+template <int PPL>
+__device__ __forceinline__ void store_flags(uint8_t* dst, uint64_t fl) {
+  if constexpr (PPL == 8)
+    *reinterpret_cast<uint64_t*>(dst) = fl;
+  else if constexpr (PPL == 4)
+    *reinterpret_cast<uint32_t*>(dst) = (uint32_t)fl;
+  else
+    *reinterpret_cast<uint16_t*>(dst) = (uint16_t)fl;
+}
+
+// Phase 1 (fused): extraction of all pixels into LDS: keys, flags, and each
+// wavefront's run of flagged pixels (D >= the boundary or the picture
+// threshold: the only pixels that can enter the mask) with their number
+// returned.  A group's keys and flags are stored whole: the padding pixels
+// of the last group get flags 0 (their thresholds are the largest int32).
 template <int EX, int PPL, int W, int CH, int NT>
 __device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __restrict__ ev, TelSmem& sm) {
   const int N = c.n_pix, np = c.n_pix_pad;
+  const int wave = threadIdx.x / kWave;
   const __amdgpu_buffer_rsrc_t r = event_rsrc(ev, c.event_elems);
-  int nlow = 0;
-  extract_event<EX, PPL, W, CH, NT>(c, r, ev, sm.rows, &sm.start, sm.xrow, [&](int pix0, const uint32_t (&key)[PPL],
+  uint16_t* cand = sm.list + wave * (kMaxPix / (NT / kWave));
+  int ncand = 0, nlow = 0;
+  if (threadIdx.x < kMaxWords) sm.mbits[threadIdx.x] = 0ull;
+  extract_event<EX, PPL, W, CH, NT>(c, r, ev, sm.rows, &sm.start, sm.list, [&](int pix0, const uint32_t (&key)[PPL],
                                                                                 uint32_t sw) {
-    if (pix0 >= N) return;
+    const bool mine = pix0 < N;
+    const int q0 = mine ? pix0 : 0;
     int32_t P[PPL], Tb[PPL], Tp[PPL];
-    load_i32<PPL>(P, c.P256 + pix0);
-    load_i32<PPL>(Tb, c.thr_bnd + pix0);
-    load_i32<PPL>(Tp, c.thr_pic + pix0);
+    load_i32<PPL>(P, c.P256 + q0);
+    load_i32<PPL>(Tb, c.thr_bnd + q0);
+    load_i32<PPL>(Tp, c.thr_pic + q0);
+    uint64_t fl = 0;  // one flag byte per pixel
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
-      const int i = pix0 + p;
-      if (i < N) {
-        const int g = (sw >> p) & 1u;
-        int32_t Pv = P[p], tb = Tb[p], tp = Tp[p];
-        if (g) { Pv = c.P256[np + i]; tb = c.thr_bnd[np + i]; tp = c.thr_pic[np + i]; }
-        const int32_t d = key_to_d<W>(key[p], Pv);
-        sm.key[i] = key[p];
-        sm.flag[i] = (uint8_t)((uint32_t)(d >= tb) | ((uint32_t)(d >= tp) << 1) | ((uint32_t)g << 2));
-        nlow += g;
-      }
+      const int g = mine ? (int)((sw >> p) & 1u) : 0;
+      int32_t Pv = P[p], tb = Tb[p], tp = Tp[p];
+      if (g) { Pv = c.P256[np + q0 + p]; tb = c.thr_bnd[np + q0 + p]; tp = c.thr_pic[np + q0 + p]; }
+      const int32_t d = key_to_d<W>(key[p], Pv);
+      const uint32_t f = (uint32_t)(d >= tb) | ((uint32_t)(d >= tp) << 1);
+      fl |= (uint64_t)(f | ((uint32_t)g << 2)) << (8 * p);
+      const uint64_t has = __ballot(mine && f != 0u);
+      if (mine && f != 0u)
+        cand[ncand + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u))] =
+            (uint16_t)(q0 + p);
+      ncand += __popcll(has);
+      if (__ballot(g != 0)) nlow += __popcll(__ballot(g != 0 && q0 + p < N));
+    }
+    if (mine) {
+      store_keys<PPL>(sm.key + pix0, key);
+      store_flags<PPL>(sm.flag + pix0, fl);
     }
   });
-  return nlow;
+  if ((threadIdx.x & (kWave - 1)) == 0) sm.nlow_w[wave] = nlow;
+  return ncand;
 }
 
-// Phase 2: mask words from the flags (needs flags of all pixels).
+// Whether a pixel with own flags f and neighbour row nv enters the mask.
+__device__ __forceinline__ bool passes(const TelSmem& sm, uint32_t f, const int4& nv) {
+  const int32_t nb2[3] = {nv.x, nv.y, nv.z};
+  uint32_t any = 0;
+#pragma unroll
+  for (int h = 0; h < 3; ++h) {
+    const int j0 = (int16_t)nb2[h], j1 = nb2[h] >> 16;
+    if (j0 >= 0) any |= sm.flag[j0];
+    if (j1 >= 0) any |= sm.flag[j1];
+  }
+  return ((f & 1u) && (any & 2u)) || ((f & 2u) && (any & 1u));
+}
+
+__device__ __forceinline__ int4 neighbour_row(const DevCam& c, int i) {
+  return *reinterpret_cast<const int4*>(c.nbr + (size_t)i * kNbrCols);
+}
+
+// Mask words from given flags of all pixels (unfused cleaning).
 template <int NT>
 __device__ __forceinline__ void mask_phase(const DevCam& c, TelSmem& sm) {
   const int N = c.n_pix, nw = (N + 63) >> 6;
   const int lane = threadIdx.x & (kWave - 1);
   for (int base = threadIdx.x & ~(kWave - 1); base < nw * kWave; base += NT) {
     const int i = base + lane;
+    const uint32_t f = i < N ? sm.flag[i] & 3u : 0u;
     bool m = false;
-    if (i < N) {
-      const uint32_t f = sm.flag[i] & 3u;
-      if (f) {
-        const int4 nv = *reinterpret_cast<const int4*>(c.nbr + (size_t)i * kNbrCols);
-        const int16_t* nb = reinterpret_cast<const int16_t*>(&nv);
-        uint32_t any = 0;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-          const int j = nb[k];
-          if (j >= 0) any |= sm.flag[j];
-        }
-        m = ((f & 1u) && (any & 2u)) || ((f & 2u) && (any & 1u));
-      }
-    }
+    if (f) m = passes(sm, f, neighbour_row(c, i));
     const uint64_t b = __ballot(m);
     if (lane == 0) sm.mbits[base >> 6] = b;
   }
 }
 
-// Phase 3: exclusive prefix of the mask-word popcounts (one wavefront).
-__device__ __forceinline__ void scan_phase(int N, TelSmem& sm) {
+// Exclusive prefix of the mask-word popcounts, by every wavefront for itself
+// (no barrier): lane w returns the base slot of word w, total the number of
+// mask pixels.  Every wavefront also writes the same bases to sm.wbase, for
+// its own lookups at any word.
+__device__ __forceinline__ int scan_phase(int N, TelSmem& sm, int* total) {
   const int nw = (N + 63) >> 6;
-  if (threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
-    const int cnt = lane < nw ? __popcll(sm.mbits[lane]) : 0;
-    int inc = cnt;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int o = __shfl_up(inc, off, kWave);
-      if (lane >= off) inc += o;
-    }
-    if (lane < nw) sm.wbase[lane] = inc - cnt;
-    if (lane == nw - 1) sm.wbase[nw] = inc;
-  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const int cnt = lane < nw ? __popcll(sm.mbits[lane]) : 0;
+  int inc = cnt;  // inclusive prefix by lane moves: within rows of 16, then across them
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xF, 0xF, false);  // row_shr:1
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xF, 0xF, false);  // row_shr:2
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xF, 0xF, false);  // row_shr:4
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xF, 0xF, false);  // row_shr:8
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  static_assert(kMaxWords <= kWave, "one mask word per lane");
+  if (lane < nw) sm.wbase[lane] = inc - cnt;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  *total = __builtin_amdgcn_readlane(inc, kWave - 1);
+  return inc - cnt;
 }
 
-// Phase 4: slot list of cleaned pixels with q, x, y, t.  FUSED takes D /
-// gain / s* from LDS and re-reads the window samples for t; otherwise D,
-// gain and t come from global arrays of this event.
-template <int NT, int W, bool FUSED>
-__device__ __forceinline__ void list_phase(const DevCam& c, TelSmem& sm, const uint16_t* __restrict__ ev,
-                                           const float* __restrict__ qg, const int32_t* __restrict__ Dg,
-                                           const uint8_t* __restrict__ gg, const float* __restrict__ tg) {
-  const int N = c.n_pix, nw = (N + 63) >> 6, np = c.n_pix_pad;
-  const int lane = threadIdx.x & (kWave - 1);
-  for (int base = threadIdx.x & ~(kWave - 1); base < nw * kWave; base += NT) {
-    const int i = base + lane;
-    const uint64_t bits = sm.mbits[base >> 6];
-    if ((bits >> lane) & 1ull) {
-      const int j = sm.wbase[base >> 6] + __popcll(bits & ((1ull << lane) - 1ull));
-      if constexpr (FUSED) {
-        const uint32_t k = sm.key[i];
-        const int g = (int)(sm.flag[i] >> 2);
-        const int s = 255 - (int)(k & 255u);
-        const int32_t P = c.P256[g * np + i];
-        const int32_t d = key_to_d<W>(k, P);
-        const int32_t nt = window_nt<W>(ev + (size_t)g * c.n_samp * np + i, np, s, P, nullptr);
-        sm.list[j] = (uint16_t)(i | (g << 15));
-        sm.slot.dq[j] = ((uint32_t)d & 0x0FFFFFFFu) | ((uint32_t)(s >> 4) << 28);
-        sm.slot.nt[j] = ((uint32_t)nt & 0x0FFFFFFFu) | ((uint32_t)(s & 15) << 28);
-      } else {
-        // the given charge, or D / (256 a) formed as the calibration forms q
-        const int g = gg ? (int)gg[i] : 0;
-        const float q = qg ? qg[i] : (float)Dg[i] / (256.0f * c.a[g * np + i]);
-        sm.list[j] = (uint16_t)(i | (g << 15));
-        sm.slot.dq[j] = __float_as_uint(q);
-        sm.slot.nt[j] = __float_as_uint(tg[i]);
-      }
+// What the Hillas passes take of one mask pixel.
+struct Slot {
+  float q, x, y;
+  double t;
+  bool border;
+};
+
+// Charge and peak time of a mask pixel from its window key and a re-read of
+// its window samples.
+template <int W>
+struct FusedSource {
+  const uint16_t* __restrict__ ev;
+  __device__ __forceinline__ void get(const DevCam& c, const TelSmem& sm, int i, Slot& s) const {
+    const int np = c.n_pix_pad;
+    const uint32_t k = sm.key[i];
+    const int g = (int)(sm.flag[i] >> 2), s0 = 255 - (int)(k & 255u);
+    const int32_t P = c.P256[g * np + i];
+    const int32_t d = key_to_d<W>(k, P);
+    const int32_t nt = window_nt<W>(ev + (size_t)g * c.n_samp * np + i, np, s0, P, nullptr);
+    s.q = (float)d / (256.0f * c.a[g * np + i]);
+    s.t = peak_time<W>(s0, nt, d);
+  }
+};
+
+// The same from given charges (or D and gain: D / (256 a) formed as the
+// calibration forms q) and times of this event.
+struct GivenSource {
+  const float* __restrict__ q;
+  const int32_t* __restrict__ D;
+  const uint8_t* __restrict__ gain;
+  const float* __restrict__ t;
+  __device__ __forceinline__ void get(const DevCam& c, const TelSmem&, int i, Slot& s) const {
+    s.q = q ? q[i] : (float)D[i] / (256.0f * c.a[(gain ? (int)gain[i] : 0) * c.n_pix_pad + i]);
+    s.t = (double)t[i];
+  }
+};
+
+template <class Src>
+__device__ __forceinline__ Slot load_slot(const DevCam& c, const TelSmem& sm, int i, const Src& src) {
+  Slot s;
+  s.x = c.x[i];
+  s.y = c.y[i];
+  s.border = c.border[i] != 0;
+  src.get(c, sm, i, s);
+  return s;
+}
+
+// Islands of an image of at most 64 mask pixels by one wavefront: adj holds
+// the slots adjacent to the lane's slot, symmetric over the lanes.  The
+// islands one after another by flood fill on the wave-uniform slot set: a
+// lane joins when its mask meets the set.  One step is a handful of
+// instructions without a memory access; the steps are at most the slots
+// plus the islands.  (A union-find over LDS took 2.3-7 us of a telescope's
+// chain of 13 us after the extraction, its finds and compare-and-swaps each
+// an LDS round trip; this takes 0.2-0.6 us.)
+__device__ __forceinline__ int wave_islands(int n, uint64_t adj) {
+  uint64_t todo = n == kWave ? ~0ull : (1ull << n) - 1ull;
+  int roots = 0;
+  while (todo) {
+    uint64_t comp = todo & (0ull - todo);
+    for (;;) {
+      const uint64_t next = comp | __ballot((adj & comp) != 0ull);
+      if (next == comp) break;
+      comp = next;
+    }
+    todo &= ~comp;
+    ++roots;
+  }
+  return roots;
+}
+
+// Enters the edges of slot j (pixel i, neighbour row nv) into sm.small.adj
+// (cleared before): each edge is taken from the row of its smaller pixel, as
+// in islands_phase, and entered at both ends.
+__device__ __forceinline__ void enter_edges(TelSmem& sm, int j, int i, const int4& nv) {
+  const int32_t nb2[3] = {nv.x, nv.y, nv.z};
+  unsigned long long own = 0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const int m = (k & 1) ? nb2[k >> 1] >> 16 : (int)(int16_t)nb2[k >> 1];
+    if (m > i && mask_bit(sm, m)) {
+      const int s = mask_slot(sm, m);
+      own |= 1ull << s;
+      atomicOr(&sm.small.adj[s], 1ull << j);
     }
   }
+  if (own) atomicOr(&sm.small.adj[j], own);
 }
 
 __device__ __forceinline__ int uf_find(volatile int32_t* par, int x) {
@@ -1169,22 +1359,18 @@ __device__ __forceinline__ void uf_union(int32_t* par, int a, int b) {
   }
 }
 
-// Phase 5: islands = roots of the union-find forest over mask slots.
-// Returns this thread's root count.  The per-pixel keys (no longer needed)
-// hold the parents.  WAVE: wavefront 0 alone, over at most 64 slots, the
-// barriers replaced by wavefront-scope ordering of its LDS accesses.
-template <int NT, bool WAVE>
+// Islands of an image of more than 64 mask pixels: roots of the union-find
+// forest over mask slots.  Returns this thread's root count.  The per-pixel
+// keys (no longer needed: a barrier lies behind their last use) hold the
+// parents.
+template <int NT>
 __device__ __forceinline__ int islands_phase(const DevCam& c, TelSmem& sm, int n) {
-  constexpr int STEP = WAVE ? kWave : NT;
   int32_t* par = reinterpret_cast<int32_t*>(sm.key);
-  for (int j = threadIdx.x; j < n; j += STEP) par[j] = j;
-  if constexpr (WAVE)
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  else
-    __syncthreads();
-  for (int j = threadIdx.x; j < n; j += STEP) {
-    const int i = sm.list[j] & 0x7FFF;
-    const int4 nv = *reinterpret_cast<const int4*>(c.nbr + (size_t)i * kNbrCols);
+  for (int j = threadIdx.x; j < n; j += NT) par[j] = j;
+  __syncthreads();
+  for (int j = threadIdx.x; j < n; j += NT) {
+    const int i = sm.list[j];
+    const int4 nv = neighbour_row(c, i);
     const int16_t* nb = reinterpret_cast<const int16_t*>(&nv);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -1192,16 +1378,16 @@ __device__ __forceinline__ int islands_phase(const DevCam& c, TelSmem& sm, int n
       if (m > i && mask_bit(sm, m)) uf_union(par, j, mask_slot(sm, m));
     }
   }
-  if constexpr (WAVE)
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  else
-    __syncthreads();
+  __syncthreads();
   int roots = 0;
-  for (int j = threadIdx.x; j < n; j += STEP) roots += (((volatile int32_t*)par)[j] == j);
+  for (int j = threadIdx.x; j < n; j += NT) roots += (((volatile int32_t*)par)[j] == j);
   return roots;
 }
 
-// Phase 6: Hillas reductions and the record.
+// Hillas reductions and the record (its island count is filled in by the
+// caller).  each(fn) calls fn(slot) for every mask pixel of this thread, in
+// the same order each time; l0_of(fn) returns fn(x, y) of slot 0.  WAVE:
+// wavefront 0 alone holds pixels.
 // Centre of gravity and second moments are FP32 sums of centred terms.  The
 // third pass takes the longitudinal and transverse coordinates l, w in the
 // rotated frame: skewness and kurtosis from q l^3, q l^4, the width from the
@@ -1211,27 +1397,24 @@ __device__ __forceinline__ int islands_phase(const DevCam& c, TelSmem& sm, int n
 // absolute sample numbers, so FP32 would cancel most digits of small time
 // gradients; in FP64 the centring cancels about t / spread(t) x mean(l) /
 // spread(l) digits, harmless).
-template <int NT, int W, bool FUSED, bool WAVE>
-__device__ __forceinline__ rta_hillas_rec hillas_phase(const DevCam& c, TelSmem& sm, int n, int roots, int nlow) {
-  constexpr int STEP = WAVE ? kWave : NT;
-  float v1[5] = {0.f, 0.f, 0.f, 0.f, (float)roots};
-  for (int j = threadIdx.x; j < n; j += STEP) {
-    const int i = sm.list[j] & 0x7FFF;
-    const float q = slot_q<FUSED>(c, sm, j, i);
-    v1[0] += q;
-    v1[1] += q * c.x[i];
-    v1[2] += q * c.y[i];
-    if (c.border[i]) v1[3] += q;
-  }
+template <int NT, bool WAVE, class Each, class L0>
+__device__ __forceinline__ rta_hillas_rec hillas_phase(TelSmem& sm, int n, int nlow, Each&& each, L0&& l0_of) {
+  float v1[4] = {0.f, 0.f, 0.f, 0.f};
+  each([&](const Slot& s) {
+    v1[0] += s.q;
+    v1[1] += s.q * s.x;
+    v1[2] += s.q * s.y;
+    if (s.border) v1[3] += s.q;
+  });
   if constexpr (WAVE)
     wave_sum(v1);
   else
-    block_sum<float, 5, NT>(v1, sm.red);
+    block_sum<float, 4, NT>(v1, sm.red);
   const float S = v1[0];
   rta_hillas_rec r;
   r.size = S;
   r.n_pix = n;
-  r.n_islands = (int32_t)v1[4];
+  r.n_islands = 0;
   r.n_lowgain = nlow;
   r.flags = r.n_lowgain > 0 ? RTA_FLAG_LOW_GAIN : 0u;
   if (n < 2 || !(S > 0.f)) {
@@ -1242,13 +1425,12 @@ __device__ __forceinline__ rta_hillas_rec hillas_phase(const DevCam& c, TelSmem&
   }
   const float xm = v1[1] / S, ym = v1[2] / S;
   float v2[3] = {0.f, 0.f, 0.f};
-  for (int j = threadIdx.x; j < n; j += STEP) {
-    const int i = sm.list[j] & 0x7FFF;
-    const float q = slot_q<FUSED>(c, sm, j, i), dx = c.x[i] - xm, dy = c.y[i] - ym;
+  each([&](const Slot& s) {
+    const float q = s.q, dx = s.x - xm, dy = s.y - ym;
     v2[0] += q * dx * dx;
     v2[1] += q * dy * dy;
     v2[2] += q * dx * dy;
-  }
+  });
   if constexpr (WAVE)
     wave_sum(v2);
   else
@@ -1262,29 +1444,24 @@ __device__ __forceinline__ rta_hillas_rec hillas_phase(const DevCam& c, TelSmem&
   const float cs = cosf(psi), sn = sinf(psi);
   // l of slot 0: every l equal to it (fewer than two distinct l) leaves the
   // time gradient undefined
-  float l0;
-  {
-    const int i = sm.list[0] & 0x7FFF;
-    l0 = (c.x[i] - xm) * cs + (c.y[i] - ym) * sn;
-  }
+  const float l0 = l0_of([&](float x, float y) { return (x - xm) * cs + (y - ym) * sn; });
   // q l^3, q l^4, q w^2, l, l^2, t, l t, |l - l0|
   double v3[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int j = threadIdx.x; j < n; j += STEP) {
-    const int i = sm.list[j] & 0x7FFF;
-    const float q = slot_q<FUSED>(c, sm, j, i), dx = c.x[i] - xm, dy = c.y[i] - ym;
+  each([&](const Slot& s) {
+    const float q = s.q, dx = s.x - xm, dy = s.y - ym;
     const float l = dx * cs + dy * sn;
     const float w = dy * cs - dx * sn;
     const float l2 = l * l;
     v3[0] += (double)(q * l2 * l);
     v3[1] += (double)(q * l2 * l2);
     v3[2] += (double)(q * w * w);
-    const double ld = (double)l, td = slot_t<FUSED, W>(sm, j);
+    const double ld = (double)l, td = s.t;
     v3[3] += ld;
     v3[4] += ld * ld;
     v3[5] += td;
     v3[6] += ld * td;
     v3[7] += fabs(ld - (double)l0);
-  }
+  });
   if constexpr (WAVE)
     wave_sum(v3);
   else
@@ -1312,21 +1489,194 @@ __device__ __forceinline__ rta_hillas_rec hillas_phase(const DevCam& c, TelSmem&
   return r;
 }
 
-// Phases 5 and 6 over the n mask slots; nlow: the image's low-gain pixel
-// count.  An image of at most 64 mask pixels (most images) is done by
-// wavefront 0 alone, with no barrier, while the other wavefronts return an
-// unused record at once; the sums are the same bit for bit, since the other
-// wavefronts would contribute exact zeros.  The threads of wavefront 0
-// return the record.
-template <int NT, int W, bool FUSED>
-__device__ __forceinline__ rta_hillas_rec islands_hillas(const DevCam& c, TelSmem& sm, int n, int nlow) {
-  if (n <= kWave) {
-    if (threadIdx.x >= kWave) return rta_hillas_rec{};
-    const int roots = islands_phase<NT, true>(c, sm, n);
-    return hillas_phase<NT, W, FUSED, true>(c, sm, n, roots, nlow);
+// Islands and Hillas of an image of 1 to 64 mask pixels by wavefront 0, slot
+// j in lane j: the slot stays in registers through the three Hillas passes.
+// The sums are the block's bit for bit, where the other wavefronts would
+// contribute exact zeros.
+template <int NT>
+__device__ __forceinline__ rta_hillas_rec small_image(TelSmem& sm, int n, int nlow, const Slot& s, uint64_t adj) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int roots = wave_islands(n, adj);
+  rta_hillas_rec r = hillas_phase<NT, true>(
+      sm, n, nlow,
+      [&](auto&& fn) {
+        if (lane < n) fn(s);
+      },
+      [&](auto&& fn) {
+        return fn(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.x))),
+                  __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.y))));
+      });
+  r.n_islands = roots;
+  return r;
+}
+
+__device__ __forceinline__ rta_hillas_rec empty_image(int nlow) {
+  rta_hillas_rec r;
+  r.size = 0.f;
+  r.cog_x = r.cog_y = r.length = r.width = r.psi = r.skewness = r.kurtosis = kNaN;
+  r.time_gradient = r.time_intercept = r.leakage = r.cog_dist = kNaN;
+  r.n_pix = 0;
+  r.n_islands = 0;
+  r.n_lowgain = nlow;
+  r.flags = (nlow > 0 ? RTA_FLAG_LOW_GAIN : 0u) | RTA_FLAG_HILLAS_INVALID | RTA_FLAG_TIME_INVALID;
+  return r;
+}
+
+// Hillas and islands of an image of more than 64 mask pixels by all threads:
+// the slot list from the mask words, the first slot of every thread kept in
+// registers through the passes (further ones, in images of more than NT mask
+// pixels, formed again in each), then the union-find in the keys' space.
+template <int NT, class Src>
+__device__ __forceinline__ rta_hillas_rec large_image(const DevCam& c, TelSmem& sm, int wbase, int n, int nlow,
+                                                      const Src& src) {
+  const int nw = (c.n_pix + 63) >> 6;
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int w = threadIdx.x / kWave; w < nw; w += NT / kWave) {
+    const uint64_t bits = sm.mbits[w];
+    const int first = __builtin_amdgcn_readlane(wbase, __builtin_amdgcn_readfirstlane(w));
+    if ((bits >> lane) & 1ull) sm.list[first + __popcll(bits & ((1ull << lane) - 1ull))] = (uint16_t)((w << 6) | lane);
   }
-  const int roots = islands_phase<NT, false>(c, sm, n);
-  return hillas_phase<NT, W, FUSED, false>(c, sm, n, roots, nlow);
+  __syncthreads();
+  Slot own;
+  if ((int)threadIdx.x < n) own = load_slot(c, sm, sm.list[threadIdx.x], src);
+  rta_hillas_rec r = hillas_phase<NT, false>(
+      sm, n, nlow,
+      [&](auto&& fn) {
+        if ((int)threadIdx.x < n) fn(own);
+        for (int j = (int)threadIdx.x + NT; j < n; j += NT) fn(load_slot(c, sm, sm.list[j], src));
+      },
+      [&](auto&& fn) {
+        const int i = sm.list[0];
+        return fn(c.x[i], c.y[i]);
+      });
+  int32_t roots[1] = {islands_phase<NT>(c, sm, n)};
+  block_sum<int32_t, 1, NT>(roots, sm.red);
+  r.n_islands = roots[0];
+  return r;
+}
+
+// Mask, image list, islands and Hillas of an extracted event.  Only flagged
+// pixels can be mask pixels, and they are few, so each wavefront works on its
+// run of them, one per lane (a wavefront with more than 64 takes further
+// rounds): neighbour rows loaded while other wavefronts still extract, the
+// mask decided by the neighbours' flags and entered in the mask words; the
+// loads that a mask pixel needs later (position, gain, window samples)
+// issued at once, in flight across the barrier and the prefix sum over the
+// mask words.  In an image of at most 64 mask pixels (95 % of the throughput
+// mix) every pixel's lane then writes its slot and edges, and wavefront 0
+// ends alone; the other wavefronts return an unused record.
+template <int NT, int W>
+__device__ __forceinline__ rta_hillas_rec fused_image(const DevCam& c, TelSmem& sm, int ncand,
+                                                      const uint16_t* __restrict__ ev) {
+  const int np = c.n_pix_pad, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint16_t* cand = sm.list + wave * (kMaxPix / (NT / kWave));
+  uint32_t* m32 = reinterpret_cast<uint32_t*>(sm.mbits);
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const bool has = lane < ncand;
+  const int i = has ? cand[lane] : 0;
+  const uint32_t f = has ? sm.flag[i] : 0u;
+  int4 nv = make_int4(-1, -1, -1, -1);
+  if (has) nv = neighbour_row(c, i);
+  __syncthreads();
+  if (threadIdx.x < kWave) sm.small.adj[lane] = 0ull;
+  bool in = false;
+  if (has) in = passes(sm, f, nv);
+  SmallSlot s;
+  int32_t P = 0;
+  uint32_t key = 0, x[W];
+  if (in) {
+    atomicOr(&m32[i >> 5], 1u << (i & 31));
+    const int g = (int)(f >> 2);
+    key = sm.key[i];
+    P = c.P256[g * np + i];
+    s.a = c.a[g * np + i];
+    s.x = c.x[i];
+    s.y = c.y[i];
+    s.s = (255u - (key & 255u)) | ((uint32_t)c.border[i] << 8);
+    const uint16_t* col = ev + ((size_t)g * c.n_samp + (255u - (key & 255u))) * np + i;
+#pragma unroll
+    for (int u = 0; u < W; ++u) x[u] = col[(size_t)u * np];
+  }
+  for (int b = kWave; b < ncand; b += kWave) {
+    const int j = b + lane;
+    if (j < ncand) {
+      const int i2 = cand[j];
+      if (passes(sm, sm.flag[i2], neighbour_row(c, i2))) atomicOr(&m32[i2 >> 5], 1u << (i2 & 31));
+    }
+  }
+  __syncthreads();
+  const int nlow = total_count<NT>(sm);
+  int n;
+  const int wbase = scan_phase(c.n_pix, sm, &n);
+  if (n > kWave) return large_image<NT>(c, sm, wbase, n, nlow, FusedSource<W>{ev});
+  if (n == 0) return empty_image(nlow);
+  if (in) {
+    const int j = mask_slot(sm, i);
+    s.d = key_to_d<W>(key, P);
+    s.nt = 0;
+#pragma unroll
+    for (int u = 1; u < W; ++u) s.nt += u * (256 * (int32_t)x[u] - P);
+    sm.small.slot[j] = s;
+    enter_edges(sm, j, i, nv);
+  }
+  for (int b = kWave; b < ncand; b += kWave) {
+    const int j2 = b + lane;
+    const int i2 = j2 < ncand ? cand[j2] : 0;
+    const bool in2 = j2 < ncand && mask_bit(sm, i2);
+    if (in2) {
+      const int g = (int)(sm.flag[i2] >> 2), j = mask_slot(sm, i2);
+      const uint32_t k2 = sm.key[i2];
+      const int s0 = 255 - (int)(k2 & 255u);
+      const int32_t P2 = c.P256[g * np + i2];
+      SmallSlot t;
+      t.d = key_to_d<W>(k2, P2);
+      t.nt = window_nt<W>(ev + (size_t)g * c.n_samp * np + i2, np, s0, P2, nullptr);
+      t.a = c.a[g * np + i2];
+      t.x = c.x[i2];
+      t.y = c.y[i2];
+      t.s = (uint32_t)s0 | ((uint32_t)c.border[i2] << 8);
+      sm.small.slot[j] = t;
+      enter_edges(sm, j, i2, neighbour_row(c, i2));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x >= kWave) return rta_hillas_rec{};
+  const SmallSlot t = sm.small.slot[min(lane, n - 1)];
+  Slot h;
+  h.q = (float)t.d / (256.0f * t.a);
+  h.x = t.x;
+  h.y = t.y;
+  h.t = peak_time<W>((int)(t.s & 255u), t.nt, t.d);
+  h.border = (t.s >> 8) != 0u;
+  return small_image<NT>(sm, n, nlow, h, sm.small.adj[lane]);
+}
+
+// The same from given mask words (behind a barrier), charges and times.
+template <int NT>
+__device__ __forceinline__ rta_hillas_rec given_image(const DevCam& c, TelSmem& sm, int nlow, const GivenSource& src) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int n;
+  const int wbase = scan_phase(c.n_pix, sm, &n);
+  if (n > kWave) return large_image<NT>(c, sm, wbase, n, nlow, src);
+  if (threadIdx.x >= kWave) return rta_hillas_rec{};
+  if (n == 0) return empty_image(nlow);
+  sm.small.adj[lane] = 0ull;
+  uint64_t words = __ballot(lane < ((c.n_pix + 63) >> 6) && sm.mbits[lane & (kMaxWords - 1)] != 0ull);
+  while (words) {
+    const int w = __builtin_ctzll(words);
+    words &= words - 1ull;
+    const uint64_t bits = sm.mbits[w];
+    if ((bits >> lane) & 1ull)
+      sm.list[__builtin_amdgcn_readlane(wbase, w) + __popcll(bits & ((1ull << lane) - 1ull))] =
+          (uint16_t)((w << 6) | lane);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const int i = sm.list[min(lane, n - 1)];
+  const int4 nv = neighbour_row(c, i);
+  const Slot s = load_slot(c, sm, i, src);
+  if (lane < n) enter_edges(sm, lane, i, nv);
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  return small_image<NT>(sm, n, nlow, s, ((volatile unsigned long long*)sm.small.adj)[lane]);
 }
 
 // Calibration -> cleaning -> Hillas of one camera event; the threads of
@@ -1334,16 +1684,8 @@ __device__ __forceinline__ rta_hillas_rec islands_hillas(const DevCam& c, TelSme
 template <int EX, int PPL, int W, int CH, int NT>
 __device__ __forceinline__ rta_hillas_rec process_telescope(const DevCam& c, const uint16_t* __restrict__ ev,
                                                             TelSmem& sm) {
-  post_count(sm, extract_phase<EX, PPL, W, CH, NT>(c, ev, sm));
-  __syncthreads();
-  mask_phase<NT>(c, sm);
-  __syncthreads();
-  scan_phase(c.n_pix, sm);
-  __syncthreads();
-  const int n = sm.wbase[(c.n_pix + 63) >> 6];
-  list_phase<NT, W, true>(c, sm, ev, nullptr, nullptr, nullptr, nullptr);
-  __syncthreads();
-  return islands_hillas<NT, W, true>(c, sm, n, total_count<NT>(sm));
+  const int ncand = extract_phase<EX, PPL, W, CH, NT>(c, ev, sm);
+  return fused_image<NT, W>(c, sm, ncand, ev);
 }
 
 __device__ __forceinline__ void bad_record(rta_hillas_rec* out) {
@@ -1470,15 +1812,12 @@ __global__ __launch_bounds__(NT) void k_hillas(DevCam c, const float* __restrict
     const uint64_t b = __ballot(m);
     if (lane == 0) sm.mbits[base >> 6] = b;
   }
-  post_count(sm, nlow);
+  const uint32_t nl = wave_sum_u32_last((uint32_t)nlow);
+  if (lane == kWave - 1) sm.nlow_w[threadIdx.x / kWave] = (int32_t)nl;
   __syncthreads();
-  scan_phase(N, sm);
-  __syncthreads();
-  const int n = sm.wbase[nw];
-  list_phase<NT, W, false>(c, sm, nullptr, q ? q + ob : nullptr, D ? D + ob : nullptr, gain ? gain + ob : nullptr,
-                           t + ob);
-  __syncthreads();
-  const rta_hillas_rec r = islands_hillas<NT, W, false>(c, sm, n, total_count<NT>(sm));
+  const rta_hillas_rec r =
+      given_image<NT>(c, sm, total_count<NT>(sm),
+                      GivenSource{q ? q + ob : nullptr, D ? D + ob : nullptr, gain ? gain + ob : nullptr, t + ob});
   if (threadIdx.x == 0) out[e] = r;
 }
 
@@ -1556,7 +1895,8 @@ __device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long te
 // counter until the batch is drained.
 template <int EX, int PPL, int W, int CH, int NT>
 __global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
-  __shared__ TelSmem sm;
+  __shared__ __attribute__((aligned(16))) uint8_t raw[smem_bytes<EX>()];
+  TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
   __shared__ long long s_tel;
   for (;;) {
     if (threadIdx.x == 0) s_tel = (long long)atomicAdd(a.queue, 1ull);
@@ -1575,7 +1915,8 @@ __global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
 template <int EX, int PPL, int W, int CH, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(min_waves<EX, NT>()))) void k_fused_grid(
     FusedArgs a) {
-  __shared__ TelSmem sm;
+  __shared__ __attribute__((aligned(16))) uint8_t raw[smem_bytes<EX>()];
+  TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
   fused_telescope<EX, PPL, W, CH, NT>(a, (long long)blockIdx.x, sm);
 }
 
