@@ -267,8 +267,82 @@ __device__ __forceinline__ void window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t
   }
 }
 
+// Keys of a few pixels of the wavefront's groups by the whole wavefront: lane
+// l takes the samples l, l + 64, ... of a pixel (one 2-byte load each, all in
+// flight together), gets the next W - 1 from its neighbour lanes and ranks
+// the windows that start at its own samples.  want: the pixels of this lane's
+// group, bit p; their keys are replaced.  A round takes one pixel of each p,
+// up to PPL at once.
+template <int STEP>
+__device__ __forceinline__ void partner_u32(uint32_t v, uint32_t* a, uint32_t* b);
+
+template <int PPL, int W>
+__device__ __forceinline__ void pixel_keys(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t sbase, uint32_t stride,
+                                           int T, uint32_t want, uint32_t (&key)[PPL]) {
+  constexpr int NR = (RTA_MAX_SAMP + kWave - 1) / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  uint64_t m[PPL], any = 0;
+#pragma unroll
+  for (int p = 0; p < PPL; ++p) {
+    m[p] = __ballot((want >> p) & 1u);
+    any |= m[p];
+  }
+  while (any) {
+    uint32_t x[PPL][NR];
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      if (!m[p]) continue;
+      const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)voff, __builtin_ctzll(m[p])) + 2u * p;
+#pragma unroll
+      for (int k = 0; k < NR; ++k)  // past the trace: its last sample, never ranked
+        if (k * kWave < T)
+          x[p][k] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+              r, (int)(at + (uint32_t)min(lane + k * kWave, T - 1) * stride), (int)sbase, 0);
+    }
+    any = 0;
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      if (!m[p]) continue;
+      uint32_t best = 0;
+      uint32_t nxt[W - 1];  // the current 64 samples shifted down by 1 .. W-1 lanes
+#pragma unroll
+      for (int u = 1; u < W; ++u) nxt[u - 1] = (uint32_t)__shfl((int)x[p][0], (lane + u) & (kWave - 1), kWave);
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        if (k * kWave >= T) continue;
+        const bool more = (k + 1) * kWave < T;
+        uint32_t sum = x[p][k];
+#pragma unroll
+        for (int u = 1; u < W; ++u) {
+          uint32_t nx = 0;
+          if (k + 1 < NR && more) nx = (uint32_t)__shfl((int)x[p][k + 1 < NR ? k + 1 : k], (lane + u) & (kWave - 1), kWave);
+          sum += lane + u < kWave ? nxt[u - 1] : nx;
+          nxt[u - 1] = nx;
+        }
+        const int s = lane + k * kWave;
+        if (s + W <= T) best = max(best, (sum << 8) | (uint32_t)(255 - s));
+      }
+      uint32_t a, b;
+      partner_u32<32>(best, &a, &b); best = max(a, b);
+      partner_u32<16>(best, &a, &b); best = max(a, b);
+      partner_u32<8>(best, &a, &b); best = max(a, b);
+      partner_u32<4>(best, &a, &b); best = max(a, b);
+      partner_u32<2>(best, &a, &b); best = max(a, b);
+      partner_u32<1>(best, &a, &b); best = max(a, b);
+      if (lane == __builtin_ctzll(m[p])) key[p] = best;
+      m[p] &= m[p] - 1ull;
+      any |= m[p];
+    }
+  }
+}
+
 // Extraction of one pixel group on its selected gain.  Returns the bit mask
-// of pixels that switched to low gain.
+// of pixels that switched to low gain.  Their low-gain windows: a wavefront
+// with at most 2 PPL switched pixels gathers those pixels' samples alone (a
+// pixel's T samples cost T memory sectors of 64 bytes, a re-stream of the
+// wavefront's groups 2 PPL sectors a slice); with more it streams its groups
+// again.  A switched pixel held its telescope for 10.5 us of re-stream at
+// 2048 x 128, against 2-3 us of gather.
 template <int PPL, int W, int CH>
 __device__ __forceinline__ uint32_t extract_group(const DevCam& c, __amdgpu_buffer_rsrc_t r, int pix0, int np, int T,
                                                   bool dual, uint32_t (&key)[PPL]) {
@@ -279,19 +353,23 @@ __device__ __forceinline__ uint32_t extract_group(const DevCam& c, __amdgpu_buff
   uint32_t sw = 0;
   if (dual) {
     window_argmax<PPL, W, CH, true>(r, voff, 0u, stride, T, key, rmax);
+    int n_sw = 0;
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
       const uint32_t m = (p & 1) ? hi16(rmax[p >> 1]) : lo16(rmax[p >> 1]);
-      if ((int)m >= c.hg_switch) sw |= 1u << p;
+      const bool low = (int)m >= c.hg_switch && pix0 + p < c.n_pix;
+      if (low) sw |= 1u << p;
+      n_sw += __popcll(__ballot(low));
     }
-    // re-stream the low gain when any lane of the wave owns a switched pixel
-    // (a wave-uniform branch keeps the buffer operands scalar)
-    if (__ballot(sw != 0u)) {
+    // wave-uniform branches (the buffer operands stay scalar)
+    if (n_sw > 2 * PPL) {
       uint32_t kl[PPL], unused[PPL / 2];
       window_argmax<PPL, W, CH, false>(r, voff, (uint32_t)T * stride, stride, T, kl, unused);
 #pragma unroll
       for (int p = 0; p < PPL; ++p)
         if ((sw >> p) & 1u) key[p] = kl[p];
+    } else if (n_sw > 0) {
+      pixel_keys<PPL, W>(r, voff, (uint32_t)T * stride, stride, T, sw, key);
     }
   } else {
     window_argmax<PPL, W, CH, false>(r, voff, 0u, stride, T, key, rmax);
