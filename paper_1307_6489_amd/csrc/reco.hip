@@ -2295,11 +2295,13 @@ hipError_t launch_queue_reset(unsigned long long* queue, hipStream_t st) {
   return hipGetLastError();
 }
 
+bool fused_uses_queue(int extractor, const rta_schedule& s) { return s.wg_per_cu != 0 && extractor == kExSliding; }
+
 hipError_t launch_fused(const FusedArgs& a, const rta_schedule& s, int n_cu, hipStream_t st) {
   long long grid = (long long)n_cu * s.wg_per_cu;
   if (grid > a.n_tel) grid = a.n_tel;
   if (grid < 1) grid = 1;
-  if (s.wg_per_cu == 0 || a.extractor != kExSliding) grid = 0;
+  if (!fused_uses_queue(a.extractor, s)) grid = 0;
   switch (a.window) {
     case 4: return launch_fused_w<4>(a, s, (int)grid, st);
     default: return hipErrorInvalidValue;

@@ -172,6 +172,9 @@ hipError_t launch_sam_fill(const SamDev& d, const rta_event_rec* evt, const doub
 hipError_t launch_sam_search(const SamDev& d, int end_bin, double* sig, int32_t* n_on, int32_t* n_off,
                              rta_sam_alert* alerts, int max_alerts, int32_t* n_alerts, hipStream_t st);
 hipError_t launch_queue_reset(unsigned long long* queue, hipStream_t st);
+// Whether launch_fused takes its telescopes from the queue counter (the
+// persistent form), which must then be zero.
+bool fused_uses_queue(int extractor, const rta_schedule& s);
 hipError_t launch_fused(const FusedArgs& a, const rta_schedule& s, int n_cu, hipStream_t st);
 hipError_t launch_event(const EventArgs& a, hipStream_t st);
 hipError_t launch_stamp(uint64_t* slot, hipStream_t st);
