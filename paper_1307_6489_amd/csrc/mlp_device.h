@@ -75,10 +75,70 @@ __device__ __forceinline__ void store4T(uint16_t* MT, int ldb, int f0, int b, bf
   MT[(size_t)(f0 + 3) * ldb + b] = (uint16_t)v[3];
 }
 
+// A wavefront's share of the network's weights: the A-operand fragments of
+// every layer and the biases, 132 registers, which cover the whole network
+// over the 64 lanes.  Loaded at once, a forward pass waits for memory once
+// instead of once per layer, and a wavefront that takes several tiles reads
+// the weights once.
+struct MlpFrag {
+  bf16x4 w1[4], w2[4][4], w3[4][4], w4[4];
+  f32x4 b1[4], b2[4], b3[4], b4;
+};
+
+__device__ __forceinline__ void mlp_load(const MlpDev& w, MlpFrag& f) {
+  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    f.w1[t] = load4(w.W1t, kInPad, 16 * t + col, 4 * grp);
+    f.b1[t] = bias4(w.b1, 16 * t + 4 * grp);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f.w2[t][u] = load4(w.W2t, kHid, 16 * t + col, 16 * u + 4 * grp);
+    f.b2[t] = bias4(w.b2, 16 * t + 4 * grp);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) f.w3[t][u] = load4(w.W3t, kHid, 16 * t + col, 16 * u + 4 * grp);
+    f.b3[t] = bias4(w.b3, 16 * t + 4 * grp);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) f.w4[u] = load4(w.W4t, kHid, col, 16 * u + 4 * grp);
+  f.b4 = bias4(w.b4, 4 * grp);
+}
+
 // Forward of one 16-row tile by one wavefront.  xin: B-operand tile of the
 // standardised inputs (lane: row l%16, features 4*(l/16)..+3).  Returns the
 // output accumulator (lanes 0..15: [logit, log10 E, 0, 0] of row l%16) and
 // the three hidden activations in B-operand layout.
+__device__ __forceinline__ f32x4 mlp_forward(const MlpFrag& f, bf16x4 xin, bf16x4 (&h1)[4], bf16x4 (&h2)[4],
+                                             bf16x4 (&h3)[4]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) h1[t] = relu_bf(mfma(f.w1[t], xin, f.b1[t]));
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    f32x4 acc = f.b2[t];
+#pragma unroll
+    for (int u = 0; u < 4; u += 2) acc = mfma2(f.w2[t][u], f.w2[t][u + 1], h1[u], h1[u + 1], acc);
+    h2[t] = relu_bf(acc);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    f32x4 acc = f.b3[t];
+#pragma unroll
+    for (int u = 0; u < 4; u += 2) acc = mfma2(f.w3[t][u], f.w3[t][u + 1], h2[u], h2[u + 1], acc);
+    h3[t] = relu_bf(acc);
+  }
+  f32x4 out = f.b4;
+#pragma unroll
+  for (int u = 0; u < 4; u += 2) out = mfma2(f.w4[u], f.w4[u + 1], h3[u], h3[u + 1], out);
+  return out;
+}
+
+// The same with each layer's weights loaded when it needs them, for kernels
+// whose occupancy the 132 registers would cost.
 __device__ __forceinline__ f32x4 mlp_forward_tile(const MlpDev& w, bf16x4 xin, bf16x4 (&h1)[4], bf16x4 (&h2)[4],
                                                   bf16x4 (&h3)[4]) {
   const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;

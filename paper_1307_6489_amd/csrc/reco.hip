@@ -1971,8 +1971,10 @@ __device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long te
 
 // Persistent form: a fixed grid of workgroups pulls telescopes from a global
 // counter until the batch is drained.
+// At least two wavefronts per SIMD: values hoisted out of the telescope loop
+// would otherwise push some shapes just past half the register file.
 template <int EX, int PPL, int W, int CH, int NT>
-__global__ __launch_bounds__(NT) void k_fused(FusedArgs a) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_fused(FusedArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t raw[smem_bytes<EX>()];
   TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
   __shared__ long long s_tel;
@@ -1998,20 +2000,27 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(min_waves<EX
   fused_telescope<EX, PPL, W, CH, NT>(a, (long long)blockIdx.x, sm);
 }
 
-// One wavefront per array event: stereo direction from the telescope records
-// and, when enabled, per-telescope classification (network on 16-telescope
-// MFMA tiles, box-cut fallback) aggregated into size-weighted event values.
+// Array events: stereo direction from the telescope records and, when
+// enabled, per-telescope classification aggregated into size-weighted event
+// values, in telescope order.
+//
+// NET: the network runs here, on 16-telescope MFMA tiles (box-cut fallback
+// per telescope).  SPLIT: an array event has a workgroup, whose wavefronts
+// take its tiles side by side (wavefront 0, which forms the stereo sums,
+// every fourth); the scores meet in LDS and are added in tile order.
+// Otherwise an event has a wavefront.
 constexpr int kEvtNT = 256;
-__global__ __launch_bounds__(kEvtNT) void k_event(EventArgs a) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t e = (int64_t)blockIdx.x * (kEvtNT / kWave) + (threadIdx.x / kWave);
-  if (e >= a.n_evt) return;
+template <bool NET, bool SPLIT>
+__device__ __forceinline__ void event_record(const EventArgs& a, int64_t e, const mlpdev::MlpFrag& net,
+                                             float (&tile_sum)[kEvtNT / kWave][3][16]) {
+  constexpr int NW = kEvtNT / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int64_t lo = a.evt_tel_off[e], hi = a.evt_tel_off[e + 1];
   rta_event_rec r;
   r.gammaness = kNaN;
   r.log10_energy = kNaN;
   if (!event_range_ok(lo, hi, a.n_tel)) {
-    if (lane == 0) {
+    if (lane == 0 && (!SPLIT || wave == 0)) {
       r.dir_x = r.dir_y = r.cond = kNaN;
       r.n_tel = 0;
       r.n_used = 0;
@@ -2023,74 +2032,104 @@ __global__ __launch_bounds__(kEvtNT) void k_event(EventArgs a) {
     return;
   }
   float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // A00, A01, A11, b0, b1, used
-  for (int64_t k = lo + lane; k < hi; k += kWave) {
-    const int ty = a.tel_type[k];
-    if (ty < 0 || ty >= a.n_types) continue;
-    const rta_hillas_rec h = a.tel[k];
-    if (h.flags & (RTA_FLAG_HILLAS_INVALID | RTA_FLAG_BAD_DESCRIPTOR)) continue;
-    if (!(h.length > 0.f) || !(h.width >= 0.f) || !isfinite(h.psi) || !isfinite(h.size)) continue;
-    const float ratio = h.width / h.length;
-    if (ratio > a.max_width_ratio) continue;
-    const float w = h.size * (1.0f - ratio);
-    const float f = a.focal[ty];
-    const float nx = -sinf(h.psi), ny = cosf(h.psi);
-    const float cx = h.cog_x / f, cy = h.cog_y / f;
-    const float nc = nx * cx + ny * cy;
-    v[0] += w * nx * nx;
-    v[1] += w * nx * ny;
-    v[2] += w * ny * ny;
-    v[3] += w * nc * nx;
-    v[4] += w * nc * ny;
-    v[5] += 1.f;
-  }
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off, kWave);
+  if (!SPLIT || wave == 0) {
+    for (int64_t k = lo + lane; k < hi; k += kWave) {
+      const int ty = a.tel_type[k];
+      if (ty < 0 || ty >= a.n_types) continue;
+      const rta_hillas_rec h = a.tel[k];
+      if (h.flags & (RTA_FLAG_HILLAS_INVALID | RTA_FLAG_BAD_DESCRIPTOR)) continue;
+      if (!(h.length > 0.f) || !(h.width >= 0.f) || !isfinite(h.psi) || !isfinite(h.size)) continue;
+      const float ratio = h.width / h.length;
+      if (ratio > a.max_width_ratio) continue;
+      const float w = h.size * (1.0f - ratio);
+      const float f = a.focal[ty];
+      const float nx = -sinf(h.psi), ny = cosf(h.psi);
+      const float cx = h.cog_x / f, cy = h.cog_y / f;
+      const float nc = nx * cx + ny * cy;
+      v[0] += w * nx * nx;
+      v[1] += w * nx * ny;
+      v[2] += w * ny * ny;
+      v[3] += w * nc * nx;
+      v[4] += w * nc * ny;
+      v[5] += 1.f;
+    }
+    butterfly(v);
   }
   // classification: rows = telescopes of this event, 16 per MFMA tile
   float c[3] = {0.f, 0.f, 0.f};  // sum size*score, sum size*log10E, sum size
-  if (a.have_box) {
+  if (NET || a.have_box) {
     const int col = lane & 15, grp = lane >> 4;
-    for (int64_t r0 = lo; r0 < hi; r0 += 16) {
-      float logit = 0.f, me = 0.f;
-      if (a.have_mlp && !a.tel_class) {
-        mlpdev::bf16x4 h1[4], h2[4], h3[4];
-        const mlpdev::bf16x4 xin = mlpdev::mlp_record_tile(a.mlp, a.tel, hi, r0);
-        const mlpdev::f32x4 o = mlpdev::mlp_forward_tile(a.mlp, xin, h1, h2, h3);
-        logit = o[0];
-        me = o[1];
+    // row of a tile: size, score and log10 E, or size 0 where it has none
+    auto row = [&](int64_t k, float logit, float me, float (&o)[3]) {
+      o[0] = o[1] = o[2] = 0.f;
+      if (k >= hi) return;
+      rta_hillas_rec h = a.tel[k];
+      const int ty = a.tel_type[k];
+      if (ty < 0 || ty >= a.n_types || (h.flags & (RTA_FLAG_HILLAS_INVALID | RTA_FLAG_BAD_DESCRIPTOR))) return;
+      float score, log10e;
+      if (!NET && a.tel_class) {  // classified in the reconstruction kernel
+        score = a.tel_class[2 * k];
+        log10e = a.tel_class[2 * k + 1];
+      } else {
+        const mlpdev::ClassOut co = mlpdev::classify_record(h, a.bc, NET, logit, me);
+        if (co.fallback) a.tel[k].flags = h.flags | RTA_FLAG_MLP_FALLBACK;
+        score = co.score;
+        log10e = co.log10e;
       }
-      const int64_t k = r0 + col;
-      if (grp == 0 && k < hi) {
-        rta_hillas_rec h = a.tel[k];
-        const int ty = a.tel_type[k];
-        if (ty >= 0 && ty < a.n_types && !(h.flags & (RTA_FLAG_HILLAS_INVALID | RTA_FLAG_BAD_DESCRIPTOR))) {
-          float score, log10e;
-          if (a.tel_class) {  // classified in the reconstruction kernel
-            score = a.tel_class[2 * k];
-            log10e = a.tel_class[2 * k + 1];
-          } else {
-            const mlpdev::ClassOut co = mlpdev::classify_record(h, a.bc, a.have_mlp != 0, logit, me);
-            if (co.fallback) a.tel[k].flags = h.flags | RTA_FLAG_MLP_FALLBACK;
-            score = co.score;
-            log10e = co.log10e;
-          }
-          if (isfinite(log10e) && h.size > 0.f) {
-            c[0] += h.size * score;
-            c[1] += h.size * log10e;
-            c[2] += h.size;
+      if (isfinite(log10e) && h.size > 0.f) {
+        o[0] = h.size;
+        o[1] = score;
+        o[2] = log10e;
+      }
+    };
+    auto add = [&](const float (&o)[3]) {
+      if (o[0] > 0.f) {
+        c[0] += o[0] * o[1];
+        c[1] += o[0] * o[2];
+        c[2] += o[0];
+      }
+    };
+    float o[3];
+    auto tile = [&](int64_t t0) {
+      mlpdev::bf16x4 h1[4], h2[4], h3[4];
+      const mlpdev::f32x4 z = mlpdev::mlp_forward(net, mlpdev::mlp_record_tile(a.mlp, a.tel, hi, t0), h1, h2, h3);
+      if (grp == 0) row(t0 + col, z[0], z[1], o);
+    };
+    if constexpr (SPLIT) {
+      for (int64_t r0 = lo; r0 < hi; r0 += 16 * NW) {
+        const int mine = (wave + NW - 1) & (NW - 1);  // wavefront 0 takes the last of four tiles
+        const int64_t t0 = r0 + 16 * mine;
+        if (t0 < hi) {
+          tile(t0);
+          if (grp == 0) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) tile_sum[mine][q][col] = o[q];
           }
         }
+        __syncthreads();
+        if (wave == 0 && grp == 0) {
+#pragma unroll
+          for (int t = 0; t < NW; ++t)
+            if (r0 + 16 * t < hi) {
+#pragma unroll
+              for (int q = 0; q < 3; ++q) o[q] = tile_sum[t][q][col];
+              add(o);
+            }
+        }
+        __syncthreads();
+      }
+    } else {
+      for (int64_t r0 = lo; r0 < hi; r0 += 16) {
+        if constexpr (NET)
+          tile(r0);
+        else if (grp == 0)
+          row(r0 + col, 0.f, 0.f, o);
+        if (grp == 0) add(o);
       }
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-#pragma unroll
-      for (int off = kWave / 2; off >= 1; off >>= 1) c[k] += __shfl_xor(c[k], off, kWave);
-    }
+    if (!SPLIT || wave == 0) butterfly(c);
   }
-  if (lane == 0) {
+  if (lane == 0 && (!SPLIT || wave == 0)) {
     const float A00 = v[0], A01 = v[1], A11 = v[2], b0 = v[3], b1 = v[4];
     const float tr = A00 + A11, det = A00 * A11 - A01 * A01;
     const float hd = 0.5f * (A00 - A11);
@@ -2115,6 +2154,36 @@ __global__ __launch_bounds__(kEvtNT) void k_event(EventArgs a) {
     a.out[e] = r;
     if (a.done_clock) a.done_clock[e] = wall_clock64();
   }
+}
+
+// No network: little work, bound by the launch and two dependent loads.
+__global__ __launch_bounds__(kEvtNT) void k_event(EventArgs a) {
+  float unused[kEvtNT / kWave][3][16];
+  const mlpdev::MlpFrag none = {};
+  const int64_t e = (int64_t)blockIdx.x * (kEvtNT / kWave) + threadIdx.x / kWave;
+  if (e < a.n_evt) event_record<false, false>(a, e, none, unused);
+}
+
+// Few events: a workgroup each.  Two tiles in turn behind the stereo sums,
+// each layer waiting for its weights, held 100 events of 21 telescopes for
+// 24.6 us; side by side with the weights loaded at once, 10.6 us.
+__global__ __launch_bounds__(kEvtNT) void k_event_split(EventArgs a) {
+  __shared__ float tile_sum[kEvtNT / kWave][3][16];  // size (0: not counted), score, log10 E per row of a tile
+  mlpdev::MlpFrag net;
+  mlpdev::mlp_load(a.mlp, net);
+  event_record<true, true>(a, (int64_t)blockIdx.x, net, tile_sum);
+}
+
+// Many events: persistent wavefronts that keep the network's weights in
+// registers from event to event (18 KB from L2 per event otherwise bounds it):
+// 200000 events of 2 to 40 telescopes 1873 -> 898 us.
+__global__ __launch_bounds__(kEvtNT) void k_event_stream(EventArgs a) {
+  float unused[kEvtNT / kWave][3][16];
+  mlpdev::MlpFrag net;
+  mlpdev::mlp_load(a.mlp, net);
+  const int64_t step = (int64_t)gridDim.x * (kEvtNT / kWave);
+  for (int64_t e = (int64_t)blockIdx.x * (kEvtNT / kWave) + threadIdx.x / kWave; e < a.n_evt; e += step)
+    event_record<true, false>(a, e, net, unused);
 }
 
 __global__ void k_stamp(uint64_t* slot) {
@@ -2326,10 +2395,15 @@ hipError_t launch_stamp(uint64_t* slot, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_event(const EventArgs& a, hipStream_t st) {
+hipError_t launch_event(const EventArgs& a, int n_cu, hipStream_t st) {
   const int64_t per = kEvtNT / kWave;
-  const int64_t grid = (a.n_evt + per - 1) / per;
-  hipLaunchKernelGGL(k_event, dim3((unsigned)grid), dim3(kEvtNT), 0, st, a);
+  const unsigned grid = (unsigned)((a.n_evt + per - 1) / per);
+  if (!(a.have_box && a.have_mlp && !a.tel_class))
+    hipLaunchKernelGGL(k_event, dim3(grid), dim3(kEvtNT), 0, st, a);
+  else if (a.n_evt <= 2 * (int64_t)n_cu)  // resident at once: two workgroups of 190 registers fit a compute unit
+    hipLaunchKernelGGL(k_event_split, dim3((unsigned)a.n_evt), dim3(kEvtNT), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_event_stream, dim3(grid < 2u * n_cu ? grid : 2u * n_cu), dim3(kEvtNT), 0, st, a);
   return hipGetLastError();
 }
 

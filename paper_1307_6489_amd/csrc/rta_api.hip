@@ -211,7 +211,7 @@ rta_status launch_batch(const rta_pipeline* pipe, const rta_batch* b, rta_hillas
     ea.tel_class = fa.classify ? b->tel_class : nullptr;
     ea.done_clock = b->evt_done_clock;
     ea.status = status;
-    RTA_HIP(rta::launch_event(ea, st));
+    RTA_HIP(rta::launch_event(ea, pipe->n_cu, st));
   }
   return RTA_OK;
 }
@@ -794,7 +794,7 @@ rta_status rta_stereo(rta_pipeline* pipe, const int64_t* evt_tel_off, const int3
   ea.tel = const_cast<rta_hillas_rec*>(tel);
   ea.out = evt_out;
   ea.status = pipe->d_status;
-  RTA_HIP(rta::launch_event(ea, (hipStream_t)stream));
+  RTA_HIP(rta::launch_event(ea, pipe->n_cu, (hipStream_t)stream));
   return RTA_OK;
 }
 

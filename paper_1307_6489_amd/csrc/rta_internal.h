@@ -176,7 +176,7 @@ hipError_t launch_queue_reset(unsigned long long* queue, hipStream_t st);
 // persistent form), which must then be zero.
 bool fused_uses_queue(int extractor, const rta_schedule& s);
 hipError_t launch_fused(const FusedArgs& a, const rta_schedule& s, int n_cu, hipStream_t st);
-hipError_t launch_event(const EventArgs& a, hipStream_t st);
+hipError_t launch_event(const EventArgs& a, int n_cu, hipStream_t st);
 hipError_t launch_stamp(uint64_t* slot, hipStream_t st);
 hipError_t launch_features(const rta_hillas_rec* rec, int64_t n, float* x, hipStream_t st);
 hipError_t launch_classify(const MlpDev& w, bool have_mlp, const rta_boxcut_desc& bc, const rta_hillas_rec* rec,
