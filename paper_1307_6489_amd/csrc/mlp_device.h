@@ -21,13 +21,20 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)(u >> 16);
 }
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Two values rounded to nearest even by v_cvt_pk_bf16_f32: the bits of f2bf
+// for every finite or infinite float (all 2^32 patterns compared); a NaN
+// stays a NaN.
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
 __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d) {
-  bf16x4 v;
-  v[0] = (short)f2bf(a);
-  v[1] = (short)f2bf(b);
-  v[2] = (short)f2bf(c);
-  v[3] = (short)f2bf(d);
-  return v;
+  return __builtin_bit_cast(bf16x4, u32x2{pack2(a, b), pack2(c, d)});
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -59,9 +66,13 @@ __device__ __forceinline__ f32x4 bias4(const float* b, int o) {
   return v;
 }
 
-__device__ __forceinline__ bf16x4 relu_bf(f32x4 a) {
-  return pack4(fmaxf(a[0], 0.f), fmaxf(a[1], 0.f), fmaxf(a[2], 0.f), fmaxf(a[3], 0.f));
-}
+// max(a, 0) as the median of a, 0 and infinity: the bits of fmaxf(a, 0) for
+// every float (all 2^32 patterns compared) in one instruction, where the
+// compiler puts a second one before a maximum of a matrix product to quiet
+// signalling NaNs.
+__device__ __forceinline__ float relu(float a) { return __builtin_amdgcn_fmed3f(a, 0.f, __builtin_inff()); }
+
+__device__ __forceinline__ bf16x4 relu_bf(f32x4 a) { return pack4(relu(a[0]), relu(a[1]), relu(a[2]), relu(a[3])); }
 
 // g * [h > 0] elementwise, rounded to bf16 (h is a ReLU output, >= 0).
 __device__ __forceinline__ bf16x4 mask_bf(f32x4 g, bf16x4 h) {
@@ -203,22 +214,46 @@ __device__ __forceinline__ float record_feature(const rta_hillas_rec& r, int f) 
   }
 }
 
+// Features 4 grp .. 4 grp + 3 of a record (0 past the tenth) for a lane of
+// group grp, by selects: a switch on the lane's feature index makes every
+// lane step through the branches of all.
+__device__ __forceinline__ void record_features4(const rta_hillas_rec& r, int grp, float (&x)[4]) {
+  const float lg = record_feature(r, 0);
+  x[0] = grp == 0 ? lg : grp == 1 ? r.psi : grp == 2 ? r.leakage : 0.f;
+  x[1] = grp == 0 ? r.length : grp == 1 ? r.skewness : grp == 2 ? (float)r.n_islands : 0.f;
+  x[2] = grp == 0 ? r.width : grp == 1 ? r.kurtosis : 0.f;
+  x[3] = grp == 0 ? r.cog_dist : grp == 1 ? r.time_gradient : 0.f;
+}
+
+// The lane's four standardised inputs of a record; a non-finite one is 0
+// (such rows fall back to the box cuts).  mean, stdv: at least 16 entries,
+// 0 and 1 past the tenth.
+__device__ __forceinline__ bf16x4 record_inputs(const float (&x)[4], const float (&mean)[4], const float (&stdv)[4]) {
+  float v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float z = (x[j] - mean[j]) / stdv[j];
+    v[j] = isfinite(z) ? z : 0.f;
+  }
+  return pack4(v[0], v[1], v[2], v[3]);
+}
+
+__device__ __forceinline__ void load_scale(const MlpDev& w, int grp, float (&mean)[4], float (&stdv)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    mean[j] = w.mean[4 * grp + j];
+    stdv[j] = w.stdv[4 * grp + j];
+  }
+}
+
 // Standardised input tile from records rec[r0 .. r0+15] (rows >= n are 0).
 __device__ __forceinline__ bf16x4 mlp_record_tile(const MlpDev& w, const rta_hillas_rec* rec, int64_t n, int64_t r0) {
   const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-  float v[4] = {0.f, 0.f, 0.f, 0.f};
-  if (r0 + col < n) {
-    const rta_hillas_rec r = rec[r0 + col];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int f = 4 * grp + j;
-      if (f < kIn) {
-        const float z = (record_feature(r, f) - w.mean[f]) / w.stdv[f];
-        v[j] = isfinite(z) ? z : 0.f;  // non-finite rows fall back to the box cuts
-      }
-    }
-  }
-  return pack4(v[0], v[1], v[2], v[3]);
+  if (r0 + col >= n) return pack4(0.f, 0.f, 0.f, 0.f);
+  float x[4], mean[4], stdv[4];
+  load_scale(w, grp, mean, stdv);
+  record_features4(rec[r0 + col], grp, x);
+  return record_inputs(x, mean, stdv);
 }
 
 struct ClassOut {
@@ -226,18 +261,13 @@ struct ClassOut {
   int gamma, fallback;
 };
 
-// Decision for one record given the network outputs (have_mlp) and the
-// box-cut tables.  The network is used when every feature is finite and
-// inside the trained range; otherwise the box cuts decide.
-__device__ __forceinline__ ClassOut classify_record(const rta_hillas_rec& r, const rta_boxcut_desc& bc, bool have_mlp,
-                                                    float logit, float mlp_e) {
+// Decision for one record: the network's outputs when in_range, else the box
+// cuts.  The bin tables (w_mean, w_std, l_mean, l_std) are given apart, so
+// that a kernel can keep them where it likes.
+__device__ __forceinline__ ClassOut classify_decide(const rta_hillas_rec& r, const rta_boxcut_desc& bc,
+                                                    const float* w_mean, const float* w_std, const float* l_mean,
+                                                    const float* l_std, bool in_range, float logit, float mlp_e) {
   ClassOut o;
-  bool in_range = have_mlp;
-#pragma unroll
-  for (int f = 0; f < kIn; ++f) {
-    const float v = record_feature(r, f);
-    in_range = in_range && isfinite(v) && v >= bc.feat_lo[f] && v <= bc.feat_hi[f];
-  }
   const float lgs = log10f(r.size);
   if (in_range) {
     o.score = 1.f / (1.f + expf(-logit));
@@ -247,14 +277,27 @@ __device__ __forceinline__ ClassOut classify_record(const rta_hillas_rec& r, con
   } else {
     int b = (int)floorf((lgs - bc.lgs_lo) / (bc.lgs_hi - bc.lgs_lo) * (float)bc.n_bins);
     b = b < 0 ? 0 : (b >= bc.n_bins ? bc.n_bins - 1 : b);
-    const float sw = (r.width - bc.w_mean[b]) / bc.w_std[b];
-    const float sl = (r.length - bc.l_mean[b]) / bc.l_std[b];
+    const float sw = (r.width - w_mean[b]) / w_std[b];
+    const float sl = (r.length - l_mean[b]) / l_std[b];
     o.gamma = (sw < bc.cut_w) && (sl < bc.cut_l);
     o.score = o.gamma ? 1.f : 0.f;
     o.log10e = bc.e_a + bc.e_b * lgs;
     o.fallback = 1;
   }
   return o;
+}
+
+// The same given the network outputs (have_mlp): the network is used when
+// every feature is finite and inside the trained range.
+__device__ __forceinline__ ClassOut classify_record(const rta_hillas_rec& r, const rta_boxcut_desc& bc, bool have_mlp,
+                                                    float logit, float mlp_e) {
+  bool in_range = have_mlp;
+#pragma unroll
+  for (int f = 0; f < kIn; ++f) {
+    const float v = record_feature(r, f);
+    in_range = in_range && isfinite(v) && v >= bc.feat_lo[f] && v <= bc.feat_hi[f];
+  }
+  return classify_decide(r, bc, bc.w_mean, bc.w_std, bc.l_mean, bc.l_std, in_range, logit, mlp_e);
 }
 
 }  // namespace mlpdev

@@ -90,3 +90,20 @@ def test_event_pass_forms_agree(torch_dev, n_evt):
             bound = (len(i) + 4) * 2.0 ** -23 * np.sum(w * np.abs(v)) / np.sum(w) * 2 + 1e-30
             assert abs(float(e[name][k]) - np.sum(w * v) / np.sum(w)) <= bound, (k, name)
     assert pipe.status() == 0
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 32767, 32768, 32769, 65600])
+def test_classify_rounds_agree(torch_dev, n):
+    """rta_classify's persistent wavefronts: a record's outputs do not depend
+    on the round or the row of the tile that it falls into."""
+    import torch
+    m, bc = network()
+    d = make(torch_dev, 2400)[3]
+    d = d[: n]
+    assert d.shape[0] == n
+    whole = rta.classify(m, bc, d)
+    parts = torch.cat([rta.classify(m, bc, d[a:a + 1003].contiguous()) for a in range(0, n, 1003)])
+    assert torch.equal(whole.view(torch.int32), parts.view(torch.int32))
+    box = rta.classify(None, bc, d)
+    assert bool((box[:, 3] == 1).all()) and torch.equal(box.view(torch.int32)[whole[:, 3] == 1],
+                                                        whole.view(torch.int32)[whole[:, 3] == 1])
