@@ -267,15 +267,71 @@ __device__ __forceinline__ void window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t
   }
 }
 
+// The two partners of a lane in one step of a butterfly over the wavefront
+// (see butterfly below), as register moves.
+template <int STEP>
+__device__ __forceinline__ void partner_u32(uint32_t v, uint32_t* a, uint32_t* b) {
+  if constexpr (STEP == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    *a = r[0];
+    *b = r[1];
+  } else if constexpr (STEP == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    *a = r[0];
+    *b = r[1];
+  } else {
+    constexpr int ctrl = STEP == 8 ? 0x128 : STEP == 4 ? 0x124 : STEP == 2 ? 0x4E : 0xB1;
+    *a = v;
+    *b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, false);
+  }
+}
+
+// Maximum over the wavefront, in every lane.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  uint32_t a, b;
+  partner_u32<32>(v, &a, &b); v = max(a, b);
+  partner_u32<16>(v, &a, &b); v = max(a, b);
+  partner_u32<8>(v, &a, &b); v = max(a, b);
+  partner_u32<4>(v, &a, &b); v = max(a, b);
+  partner_u32<2>(v, &a, &b); v = max(a, b);
+  partner_u32<1>(v, &a, &b); v = max(a, b);
+  return v;
+}
+
+// Best window of a trace spread over the wavefront, lane l holding samples
+// l, l + 64, ... in x (any value past the trace): the largest
+// (sum << 8) | (255 - start), in every lane.
+template <int W, int NR>
+__device__ __forceinline__ uint32_t wave_window(const uint32_t (&x)[NR], int T) {
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t best = 0;
+  uint32_t nxt[W - 1];  // the current 64 samples shifted down by 1 .. W-1 lanes
+#pragma unroll
+  for (int u = 1; u < W; ++u) nxt[u - 1] = (uint32_t)__shfl((int)x[0], (lane + u) & (kWave - 1), kWave);
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    if (k * kWave >= T) continue;
+    const bool more = (k + 1) * kWave < T;
+    uint32_t sum = x[k];
+#pragma unroll
+    for (int u = 1; u < W; ++u) {
+      uint32_t nx = 0;
+      if (k + 1 < NR && more) nx = (uint32_t)__shfl((int)x[k + 1 < NR ? k + 1 : k], (lane + u) & (kWave - 1), kWave);
+      sum += lane + u < kWave ? nxt[u - 1] : nx;
+      nxt[u - 1] = nx;
+    }
+    const int s = lane + k * kWave;
+    if (s + W <= T) best = max(best, (sum << 8) | (uint32_t)(255 - s));
+  }
+  return wave_max_u32(best);
+}
+
 // Keys of a few pixels of the wavefront's groups by the whole wavefront: lane
 // l takes the samples l, l + 64, ... of a pixel (one 2-byte load each, all in
 // flight together), gets the next W - 1 from its neighbour lanes and ranks
 // the windows that start at its own samples.  want: the pixels of this lane's
 // group, bit p; their keys are replaced.  A round takes one pixel of each p,
 // up to PPL at once.
-template <int STEP>
-__device__ __forceinline__ void partner_u32(uint32_t v, uint32_t* a, uint32_t* b);
-
 template <int PPL, int W>
 __device__ __forceinline__ void pixel_keys(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t sbase, uint32_t stride,
                                            int T, uint32_t want, uint32_t (&key)[PPL]) {
@@ -303,32 +359,7 @@ __device__ __forceinline__ void pixel_keys(__amdgpu_buffer_rsrc_t r, uint32_t vo
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
       if (!m[p]) continue;
-      uint32_t best = 0;
-      uint32_t nxt[W - 1];  // the current 64 samples shifted down by 1 .. W-1 lanes
-#pragma unroll
-      for (int u = 1; u < W; ++u) nxt[u - 1] = (uint32_t)__shfl((int)x[p][0], (lane + u) & (kWave - 1), kWave);
-#pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        if (k * kWave >= T) continue;
-        const bool more = (k + 1) * kWave < T;
-        uint32_t sum = x[p][k];
-#pragma unroll
-        for (int u = 1; u < W; ++u) {
-          uint32_t nx = 0;
-          if (k + 1 < NR && more) nx = (uint32_t)__shfl((int)x[p][k + 1 < NR ? k + 1 : k], (lane + u) & (kWave - 1), kWave);
-          sum += lane + u < kWave ? nxt[u - 1] : nx;
-          nxt[u - 1] = nx;
-        }
-        const int s = lane + k * kWave;
-        if (s + W <= T) best = max(best, (sum << 8) | (uint32_t)(255 - s));
-      }
-      uint32_t a, b;
-      partner_u32<32>(best, &a, &b); best = max(a, b);
-      partner_u32<16>(best, &a, &b); best = max(a, b);
-      partner_u32<8>(best, &a, &b); best = max(a, b);
-      partner_u32<4>(best, &a, &b); best = max(a, b);
-      partner_u32<2>(best, &a, &b); best = max(a, b);
-      partner_u32<1>(best, &a, &b); best = max(a, b);
+      const uint32_t best = wave_window<W>(x[p], T);
       if (lane == __builtin_ctzll(m[p])) key[p] = best;
       m[p] &= m[p] - 1ull;
       any |= m[p];
@@ -548,6 +579,9 @@ enum : int {
 
 // Neighbour peak: high-gain slices staged in LDS this many at a time.
 constexpr int kNbrRows = 4;
+// Most pixels whose neighbour windows are formed apart, and most staged
+// traces (with those, eight slices fit at once).
+constexpr int kNbrAsk = 512, kNbrStage = 600;
 
 // Sums of the W samples from slice s on of every pixel of the group (one
 // load per slice) and, with TRACK_MAX, their packed per-pixel maximum.
@@ -759,39 +793,39 @@ __device__ __forceinline__ int global_start(const uint32_t* rows, int T, int32_t
 // W_j(s).  Four high-gain slices at a time are staged in LDS transposed,
 // one 64-bit word of four halfwords per pixel (slices k0..k0+3; word Npad = 0
 // stands in for a missing neighbour), so a pixel's neighbours cost one 8-byte
-// read each per four slices, and the per-slice neighbour sums y(t) come from
-// packed dot products.  The next four slices are loaded while the current
-// ones are used.  Words sit at the pixels' lattice-row positions, and in this
-// stage lane t takes positions t, t + NT, ...: the lanes of one read are
-// neighbours along a row, so each direction's neighbour words are (nearly)
+// read each per four slices.  The next four slices are loaded while the
+// current ones are used.  Words sit at the pixels' lattice-row positions, and
+// in this stage lane t takes positions t, t + NT, ...: the lanes of one read
+// are neighbours along a row, so each direction's neighbour words are (nearly)
 // consecutive; the pixels' best keys then go through LDS to the lanes'
-// PPL-pixel groups.  Each lane keeps, for each of its pixels, the last
-// W-1 sums to form C(t-W+1), the best key (C << 8) | (255 - s) and the raw
-// high-gain maximum (gain decision on the whole trace, as for the sliding
-// window); a step whose four slices all end a window inside the trace forms
-// its four window sums at once.  Then the pixel's own W samples at its start
-// on its selected gain give S.  Called by every thread of the block
-// (contains barriers).
-template <int PPL, int W, int NT, class Fn>
-__device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer_rsrc_t r,
-                                                const uint16_t* __restrict__ ev, uint16_t* xrow, uint32_t* keys,
-                                                Fn&& fn) {
-  static_assert(kNbrRows == 4, "four slices per staged pixel word pair");
+// PPL-pixel groups.  The raw high-gain maximum (gain decision on the whole
+// trace, as for the sliding window) is kept where the slices are staged.
+//
+// nbr_scan makes the pass over the slices.  With EXACT, the neighbour and
+// window sums are formed in 32 bits.  Without, everything stays in saturating
+// packed 16-bit halves, two slices to a register: the neighbour sums, the
+// window sums C(k) = p(k) + p(k - 2) with p(k) = y(k) + y(k - 1) (one funnel
+// shift per two slices gives the pairs), and a key is one byte permute of
+// the halfword with the slice's index byte: 24 vector instructions per pixel
+// and four slices where the 32-bit form takes about 50 (the mix 1123 -> 1042
+// us: the scan waits more for LDS and barriers than for them).  A best sum of 65535
+// says that some sum may not have fitted, and the event is scanned again in
+// 32 bits (returned true; an image has to put some 8500 p.e. into six
+// pixels); a camera whose pedestals alone bring the sums near that
+// (DevCam::nbr_exact) is scanned in 32 bits at once.
+template <int W, int NT, bool EXACT>
+__device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t r, uint64_t* xs, uint32_t* keys,
+                                         uint8_t* low, int32_t* again) {
+  static_assert(kNbrRows == 4 && W == 4, "four slices per staged pixel word pair, windows of four");
   constexpr int MAXK = (kMaxPix + NT - 1) / NT;  // pixels per lane: t, t + NT, ...
-  constexpr int MAXP = (kMaxPix + NT * PPL - 1) / (NT * PPL);
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
-  const bool dual = c.n_gain == 2;
-  const int npass = (N + NT * PPL - 1) / (NT * PPL);
-  // staged words: slices k0, k0+1 in the low dword, k0+2, k0+3 in the high
-  // one (64-bit words: the packed dot of a two-lane vector's second element
-  // has been seen compiled onto its first)
-  uint64_t* xs = reinterpret_cast<uint64_t*>(xrow);
   // position p = 8 g + m lives in word 8 g + (m ^ (g & 7)): consecutive
   // lanes reading consecutive positions touch distinct banks
   auto slot = [](uint32_t j) { return (j & ~7u) | ((j ^ (j >> 3)) & 7u); };
   uint32_t nb[MAXK][3];  // six neighbour words per position: LDS byte offsets, 16 bits each (word Npad if missing)
-  uint32_t ring[MAXK][W - 1];
-  uint32_t best[MAXK], hmax2[MAXK];
+  uint32_t best[MAXK];
+  us2 yq[EXACT ? 1 : MAXK], pq[EXACT ? 1 : MAXK];  // y(k0-2), y(k0-1) and p(k0-2), p(k0-1)
+  uint32_t ring[EXACT ? MAXK : 1][W - 1];          // y(k0-1), y(k0-2), y(k0-3)
 #pragma unroll
   for (int k = 0; k < MAXK; ++k) {
     const int p = (int)threadIdx.x + k * NT;
@@ -806,12 +840,18 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
         nb[k][h] = (lo << 3) | (hi << 19);  // (Npad + 1) * 8 bytes < 2^16
       }
     }
+    if constexpr (EXACT) {
 #pragma unroll
-    for (int u = 0; u < W - 1; ++u) ring[k][u] = 0;
+      for (int u = 0; u < W - 1; ++u) ring[k][u] = 0;
+    } else {
+      yq[k] = pq[k] = us2{0, 0};
+    }
     best[k] = 0;
-    hmax2[k] = 0;
   }
-  if (threadIdx.x == 0) xs[np] = 0ull;
+  if (threadIdx.x == 0) {
+    xs[np] = 0ull;
+    *again = 0;
+  }
   // thread q stages 16-byte pixel group q (np / 8 <= kMaxPix / 8 <= NT
   // groups), the next four slices loaded while the current ones are used
   static_assert(kMaxPix / 8 <= NT, "one staged pixel group per thread");
@@ -826,7 +866,7 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
 #pragma unroll
     for (int m = 0; m < 8; ++m) dst[m] = slot((w4[m >> 1] >> ((m & 1) * 16)) & 0xffffu);
   }
-  u32x4 d[kNbrRows];
+  u32x4 d[kNbrRows], hmax = {0, 0, 0, 0};
   auto load4 = [&](int k0) {
 #pragma unroll
     for (int k = 0; k < kNbrRows; ++k)
@@ -846,38 +886,33 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
       for (int m = 0; m < 8; ++m) {
         const uint32_t sel = (m & 1) ? 0x07060302u : 0x05040100u;  // high / low halfwords
         xs[dst[m]] = (uint64_t)__builtin_amdgcn_perm(d[1][m >> 1], d[0][m >> 1], sel) |
-                                    ((uint64_t)__builtin_amdgcn_perm(d[3][m >> 1], d[2][m >> 1], sel) << 32);
+                     ((uint64_t)__builtin_amdgcn_perm(d[3][m >> 1], d[2][m >> 1], sel) << 32);
       }
+#pragma unroll
+      for (int k = 0; k < kNbrRows; ++k)
+        if (k0 + k < T) {
+#pragma unroll
+          for (int h = 0; h < 4; ++h) hmax[h] = pkmax16(hmax[h], d[k][h]);
+        }
     }
     __syncthreads();
     if (stager && k0 + kNbrRows < T) load4(k0 + kNbrRows);
     // uniform: every slice of this step has a full window inside the trace
     const bool full = k0 >= W - 1 && k0 + kNbrRows <= T;
     const uint32_t key0 = (uint32_t)(255 - (k0 - (W - 1)));  // 255 - window start of slice k0
-#pragma unroll
-    for (int k = 0; k < MAXK; ++k) {
-      const int p = (int)threadIdx.x + k * NT;
-      if (p >= N) continue;
+    // the four slices' index bytes (slices without a window are not ranked)
+    const uint32_t idx = (key0 & 255u) | (((key0 - 1u) & 255u) << 8) | (((key0 - 2u) & 255u) << 16) |
+                         (((key0 - 3u) & 255u) << 24);
+    // positions past the camera read the zero word; their keys are not used
+    auto take = [&](int k, bool whole) {
       uint64_t v[6];
 #pragma unroll
       for (int m = 0; m < 6; ++m) {
         const uint32_t off = (nb[k][m >> 1] >> ((m & 1) * 16)) & 0xffffu;
         v[m] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(xs) + off);
       }
-      // the six neighbours' slices summed two at a time in saturating 16-bit
-      // halves; a sum that reached 65535 (so maybe more) is formed again in
-      // 32 bits, for the whole wave when any lane needs it
-      us2 s01 = __builtin_bit_cast(us2, (uint32_t)v[0]), s23 = __builtin_bit_cast(us2, (uint32_t)(v[0] >> 32));
-#pragma unroll
-      for (int m = 1; m < 6; ++m) {
-        s01 = __builtin_elementwise_add_sat(s01, __builtin_bit_cast(us2, (uint32_t)v[m]));
-        s23 = __builtin_elementwise_add_sat(s23, __builtin_bit_cast(us2, (uint32_t)(v[m] >> 32)));
-      }
-      const us2 smax = __builtin_elementwise_max(s01, s23);
-      uint32_t y[kNbrRows] = {s01[0], s01[1], s23[0], s23[1]};
-      if (__ballot(smax[0] == 0xffffu || smax[1] == 0xffffu)) {
-#pragma unroll
-        for (int u = 0; u < kNbrRows; ++u) y[u] = 0;
+      if constexpr (EXACT) {
+        uint32_t y[kNbrRows] = {0, 0, 0, 0};
 #pragma unroll
         for (int m = 0; m < 6; ++m) {
           const uint32_t v01 = (uint32_t)v[m], v23 = (uint32_t)(v[m] >> 32);
@@ -886,58 +921,105 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
           y[2] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_lo, y[2], false);
           y[3] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_hi, y[3], false);
         }
+#pragma unroll
+        for (int u = 0; u < kNbrRows; ++u) {
+          const int t = k0 + u;
+          if (t >= T) break;
+          uint32_t C = y[u];
+#pragma unroll
+          for (int z = 0; z < W - 1; ++z) C += ring[k][z];
+          if (t >= W - 1) best[k] = max(best[k], (C << 8) | (uint32_t)(255 - (t - (W - 1))));
+#pragma unroll
+          for (int z = W - 2; z > 0; --z) ring[k][z] = ring[k][z - 1];
+          ring[k][0] = y[u];
+        }
+      } else {
+        us2 s01 = __builtin_bit_cast(us2, (uint32_t)v[0]), s23 = __builtin_bit_cast(us2, (uint32_t)(v[0] >> 32));
+#pragma unroll
+        for (int m = 1; m < 6; ++m) {
+          s01 = __builtin_elementwise_add_sat(s01, __builtin_bit_cast(us2, (uint32_t)v[m]));
+          s23 = __builtin_elementwise_add_sat(s23, __builtin_bit_cast(us2, (uint32_t)(v[m] >> 32)));
+        }
+        // (y(k0-1), y(k0)) and (y(k0+1), y(k0+2))
+        const us2 m10 = __builtin_bit_cast(us2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, s01),
+                                                                          __builtin_bit_cast(uint32_t, yq[k]), 16));
+        const us2 s12 = __builtin_bit_cast(us2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, s23),
+                                                                          __builtin_bit_cast(uint32_t, s01), 16));
+        const us2 p01 = __builtin_elementwise_add_sat(s01, m10), p23 = __builtin_elementwise_add_sat(s23, s12);
+        const uint32_t C01 = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(p01, pq[k]));
+        const uint32_t C23 = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(p23, p01));
+        yq[k] = s23;
+        pq[k] = p23;
+        // (C << 8) | index byte: bytes 4..7 of the permute are C's, 0..3 the indices'
+        const uint32_t kk[kNbrRows] = {__builtin_amdgcn_perm(C01, idx, 0x0c050400u),
+                                       __builtin_amdgcn_perm(C01, idx, 0x0c070601u),
+                                       __builtin_amdgcn_perm(C23, idx, 0x0c050402u),
+                                       __builtin_amdgcn_perm(C23, idx, 0x0c070603u)};
+        if (whole) {
+          best[k] = max(max(best[k], kk[0]), kk[1]);
+          best[k] = max(max(best[k], kk[2]), kk[3]);
+        } else {
+#pragma unroll
+          for (int u = 0; u < kNbrRows; ++u)
+            if (k0 + u >= W - 1 && k0 + u < T) best[k] = max(best[k], kk[u]);
+        }
       }
-      const uint64_t own = xs[slot((uint32_t)p)];
-      const uint32_t o01 = (uint32_t)own, o23 = (uint32_t)(own >> 32);
-      if constexpr (W == kNbrRows) if (full) {
-        // all four slices inside the trace and past the first window: the
-        // four window sums C(k0 + u) = y(k0 + u - 3) + ... + y(k0 + u) from
-        // the ring (ring[z] = y(k0 - 1 - z)) and this step's sums, the
-        // ring shifted once, the high-gain maximum on packed halfwords
-        const us2 hm = __builtin_elementwise_max(
-            __builtin_elementwise_max(__builtin_bit_cast(us2, hmax2[k]), __builtin_bit_cast(us2, o01)),
-            __builtin_bit_cast(us2, o23));
-        hmax2[k] = __builtin_bit_cast(uint32_t, hm);
-        const uint32_t r01 = ring[k][0] + ring[k][1], y01 = y[0] + y[1];
-        const uint32_t C0 = y[0] + r01 + ring[k][2], C1 = y[1] + y[0] + r01;
-        const uint32_t C2 = y[2] + y01 + ring[k][0], C3 = y[3] + y[2] + y01;
-        best[k] = max(best[k], (C0 << 8) | key0);
-        best[k] = max(best[k], (C1 << 8) | (key0 - 1u));
-        best[k] = max(best[k], (C2 << 8) | (key0 - 2u));
-        best[k] = max(best[k], (C3 << 8) | (key0 - 3u));
-        ring[k][0] = y[3];
-        ring[k][1] = y[2];
-        ring[k][2] = y[1];
-        continue;
-      }
-      const uint32_t xo[kNbrRows] = {lo16(o01), hi16(o01), lo16(o23), hi16(o23)};
+    };
+    // two positions at a time without a branch between them, so that the
+    // second's reads are in flight during the first's sums
 #pragma unroll
-      for (int u = 0; u < kNbrRows; ++u) {
-        const int t = k0 + u;
-        if (t >= T) break;
-        hmax2[k] = max(hmax2[k] & 0xffffu, xo[u]) | (hmax2[k] & 0xffff0000u);
-        uint32_t C = y[u];
-#pragma unroll
-        for (int z = 0; z < W - 1; ++z) C += ring[k][z];
-        if (t >= W - 1) best[k] = max(best[k], (C << 8) | (uint32_t)(255 - (t - (W - 1))));
-#pragma unroll
-        for (int z = W - 2; z > 0; --z) ring[k][z] = ring[k][z - 1];
-        ring[k][0] = y[u];
+    for (int k = 0; k < MAXK; k += 2) {
+      if (k * NT >= N) continue;
+      if (!EXACT && full) {
+        take(k, true);
+        if (k + 1 < MAXK) take(k + 1, true);
+      } else {
+        take(k, false);
+        if (k + 1 < MAXK) take(k + 1, false);
       }
     }
   }
-  // hand the keys over to the lanes' pixel groups: the best key of each
-  // pixel (C < 2^21, so bits 29..31 are free) with bit 31 = low gain
+  // hand the keys over to the lanes' pixel groups, the low-gain decisions by
+  // their own bytes
 #pragma unroll
   for (int k = 0; k < MAXK; ++k) {
     const int p = (int)threadIdx.x + k * NT;
-    const uint32_t hm = max(lo16(hmax2[k]), hi16(hmax2[k]));
     if (p < N) {
-      const uint32_t pix = (uint32_t)c.lat[(size_t)p * kNbrCols + 6] & 0xffffu;  // the pixel at position p
-      keys[pix] = best[k] | ((dual && (int)hm >= c.hg_switch) ? 0x80000000u : 0u);
+      keys[(uint32_t)c.lat[(size_t)p * kNbrCols + 6] & 0xffffu] = best[k];  // the pixel at position p
+      if (!EXACT && best[k] >= 0xffff00u) *again = 1;
     }
   }
+  if (stager) {
+    uint64_t b = 0;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const uint32_t x = (m & 1) ? hi16(hmax[m >> 1]) : lo16(hmax[m >> 1]);
+      b |= (uint64_t)(c.n_gain == 2 && (int)x >= c.hg_switch && q * 8 + m < N) << (8 * m);
+    }
+    *reinterpret_cast<uint64_t*>(low + q * 8) = b;
+  }
   __syncthreads();
+  return !EXACT && *again != 0;
+}
+
+// The neighbour peak's keys of every pixel group: the scan, then the pixel's
+// own W samples at its start on its selected gain give S.  Called by every
+// thread of the block (contains barriers).
+template <int PPL, int W, int NT, class Fn>
+__device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer_rsrc_t r,
+                                                const uint16_t* __restrict__ ev, uint16_t* xrow, uint32_t* keys,
+                                                uint8_t* low, int32_t* again, Fn&& fn) {
+  constexpr int MAXP = (kMaxPix + NT * PPL - 1) / (NT * PPL);
+  const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
+  const int npass = (N + NT * PPL - 1) / (NT * PPL);
+  // staged words: slices k0, k0+1 in the low dword, k0+2, k0+3 in the high one
+  uint64_t* xs = reinterpret_cast<uint64_t*>(xrow);
+  bool exact = c.nbr_exact != 0;
+  if (!exact) exact = nbr_scan<W, NT, false>(c, r, xs, keys, low, again);
+  if (exact) {
+    __syncthreads();  // the flag has been read by every thread
+    nbr_scan<W, NT, true>(c, r, xs, keys, low, again);
+  }
 #pragma unroll
   for (int ps = 0; ps < MAXP; ++ps) {
     if (ps >= npass) continue;
@@ -948,10 +1030,8 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
       const int i = pix0 + p;
       key[p] = 0;
       if (i >= N) continue;
-      const uint32_t kb = keys[i];
-      const int g = (int)(kb >> 31);
+      const int g = low[i], s = 255 - (int)(keys[i] & 255u);
       sw |= (uint32_t)g << p;
-      const int s = 255 - (int)(kb & 255u);
       const uint16_t* col = ev + ((size_t)g * T + s) * np + i;
       uint32_t S = 0;
 #pragma unroll
@@ -962,13 +1042,35 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
   }
 }
 
+// Upper bounds for the neighbour peak: the sliding window's key on the high
+// gain of every pixel group, and its low-gain bits.
+template <int PPL, int W, int CH, int NT, class Fn>
+__device__ __forceinline__ void bound_event(const DevCam& c, __amdgpu_buffer_rsrc_t r, Fn&& fn) {
+  const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
+  const int npass = (N + NT * PPL - 1) / (NT * PPL);
+  for (int ps = 0; ps < npass; ++ps) {
+    const int pix0 = (ps * NT + (int)threadIdx.x) * PPL;
+    uint32_t key[PPL], rmax[PPL / 2];
+#pragma unroll
+    for (int h = 0; h < PPL / 2; ++h) rmax[h] = 0;
+    window_argmax<PPL, W, CH, true>(r, (uint32_t)pix0 * 2u, 0u, (uint32_t)np * 2u, T, key, rmax);
+    uint32_t sw = 0;
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      const uint32_t m = (p & 1) ? hi16(rmax[p >> 1]) : lo16(rmax[p >> 1]);
+      if (c.n_gain == 2 && (int)m >= c.hg_switch) sw |= 1u << p;
+    }
+    fn(pix0, key, sw);
+  }
+}
+
 // Keys of every pixel of one event, group by group: fn(pix0, key, sw) for
 // each of this thread's groups.  rows / start: LDS scratch of the global
-// peak (NT/64 * 256 words, one word); xrow: LDS slices of the neighbour
-// peak (kNbrRows * (kMaxPix + 8) halfwords).
+// peak (NT/64 * 256 words, one word); xrow, low: LDS slices of the neighbour
+// peak (kNbrRows * (kMaxPix + 8) halfwords) and a byte per pixel.
 template <int EX, int PPL, int W, int CH, int NT, class Fn>
 __device__ __forceinline__ void extract_event(const DevCam& c, __amdgpu_buffer_rsrc_t r, const uint16_t* ev,
-                                              uint32_t* rows, int32_t* start, uint16_t* xrow, Fn&& fn) {
+                                              uint32_t* rows, int32_t* start, uint16_t* xrow, uint8_t* low, Fn&& fn) {
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
   const bool dual = c.n_gain == 2;
   // Uniform pass loop: every lane streams (loads past the event read 0 from
@@ -986,7 +1088,7 @@ __device__ __forceinline__ void extract_event(const DevCam& c, __amdgpu_buffer_r
       fn(pix0, key, sw);
     }
   } else if constexpr (EX == kExNeighbour) {
-    neighbour_event<PPL, W, NT>(c, r, ev, xrow, rows, fn);
+    neighbour_event<PPL, W, NT>(c, r, ev, xrow, rows, low, start, fn);
   } else {
     constexpr int MAXP = (kMaxPix + NT * PPL - 1) / (NT * PPL);
     uint32_t* my_rows = rows + (threadIdx.x / kWave) * 256;
@@ -1084,7 +1186,6 @@ struct TelSmem {
   int32_t wbase[kMaxWords];  // slot of each word's first mask pixel
   int32_t nlow_w[16];        // per-wave counts of low-gain pixels
   int32_t start;             // global peak window start
-  // from here on the neighbour peak's staged slices overlay the rest (extraction only)
   alignas(16) uint16_t list[kMaxPix];  // flagged pixels, a run per wavefront; then slot -> pixel (large images)
   union {
     struct {
@@ -1092,13 +1193,23 @@ struct TelSmem {
       unsigned long long adj[kWave];  // slots adjacent to each slot
     } small;
     double red[16 * 8];      // cross-wave reduction scratch (large images)
+    uint16_t ask[kNbrAsk];   // neighbour peak: pixels whose windows are wanted
   };
 };
 
-constexpr size_t kXrowBytes = sizeof(uint16_t) * kNbrRows * (kMaxPix + 8);
+static_assert(sizeof(uint16_t) * kNbrAsk <= sizeof(SmallSlot) * kWave + 8 * kWave, "the list overlays the small slots");
+// The neighbour peak's workgroup: its staged slices or traces and their
+// pixels beside the rest.
+constexpr int kXrow = kNbrRows * (kMaxPix + 8);
+static_assert(kXrow / (kNbrStage + 1) >= 12, "eight slices of every staged trace fit");
+struct NbrSmem {
+  TelSmem tel;
+  alignas(16) uint16_t xrow[kXrow];
+  uint16_t px[kMaxPix];  // pixels whose traces are staged
+};
 template <int EX>
 constexpr size_t smem_bytes() {
-  return EX == kExNeighbour ? (offsetof(TelSmem, list) + kXrowBytes + 15) & ~size_t(15) : sizeof(TelSmem);
+  return EX == kExNeighbour ? sizeof(NbrSmem) : sizeof(TelSmem);
 }
 
 // Butterfly sum of a 32-bit or 64-bit value over the wavefront: every lane
@@ -1110,23 +1221,6 @@ constexpr size_t smem_bytes() {
 // lane i + 4 holds what lane i ^ 4 does) and quad permutes.  A dependent
 // step costs a few cycles where an LDS permute costs over a hundred; the
 // three reductions of an image went from 1.4 us to 0.3 us.
-template <int STEP>
-__device__ __forceinline__ void partner_u32(uint32_t v, uint32_t* a, uint32_t* b) {
-  if constexpr (STEP == 32) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    *a = r[0];
-    *b = r[1];
-  } else if constexpr (STEP == 16) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    *a = r[0];
-    *b = r[1];
-  } else {
-    constexpr int ctrl = STEP == 8 ? 0x128 : STEP == 4 ? 0x124 : STEP == 2 ? 0x4E : 0xB1;
-    *a = v;
-    *b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, false);
-  }
-}
-
 template <int STEP, typename T>
 __device__ __forceinline__ T butterfly_step(T v) {
   if constexpr (sizeof(T) == 4) {
@@ -1231,16 +1325,18 @@ __device__ __forceinline__ void store_flags(uint8_t* dst, uint64_t fl) {
 // threshold: the only pixels that can enter the mask) with their number
 // returned.  A group's keys and flags are stored whole: the padding pixels
 // of the last group get flags 0 (their thresholds are the largest int32).
-template <int EX, int PPL, int W, int CH, int NT>
-__device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __restrict__ ev, TelSmem& sm) {
+// BOUND: the windows are upper bounds of the pixels' sums, and a low-gain
+// pixel, whose sum they do not bound, counts as at both thresholds.
+template <int EX, int PPL, int W, int CH, int NT, bool BOUND>
+__device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __restrict__ ev, TelSmem& sm,
+                                             uint16_t* xrow) {
   const int N = c.n_pix, np = c.n_pix_pad;
   const int wave = threadIdx.x / kWave;
   const __amdgpu_buffer_rsrc_t r = event_rsrc(ev, c.event_elems);
   uint16_t* cand = sm.list + wave * (kMaxPix / (NT / kWave));
   int ncand = 0, nlow = 0;
   if (threadIdx.x < kMaxWords) sm.mbits[threadIdx.x] = 0ull;
-  extract_event<EX, PPL, W, CH, NT>(c, r, ev, sm.rows, &sm.start, sm.list, [&](int pix0, const uint32_t (&key)[PPL],
-                                                                                uint32_t sw) {
+  auto take = [&](int pix0, const uint32_t (&key)[PPL], uint32_t sw) {
     const bool mine = pix0 < N;
     const int q0 = mine ? pix0 : 0;
     int32_t P[PPL], Tb[PPL], Tp[PPL];
@@ -1254,7 +1350,7 @@ __device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __
       int32_t Pv = P[p], tb = Tb[p], tp = Tp[p];
       if (g) { Pv = c.P256[np + q0 + p]; tb = c.thr_bnd[np + q0 + p]; tp = c.thr_pic[np + q0 + p]; }
       const int32_t d = key_to_d<W>(key[p], Pv);
-      const uint32_t f = (uint32_t)(d >= tb) | ((uint32_t)(d >= tp) << 1);
+      const uint32_t f = BOUND && g ? 3u : (uint32_t)(d >= tb) | ((uint32_t)(d >= tp) << 1);
       fl |= (uint64_t)(f | ((uint32_t)g << 2)) << (8 * p);
       const uint64_t has = __ballot(mine && f != 0u);
       if (mine && f != 0u)
@@ -1267,7 +1363,11 @@ __device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __
       store_keys<PPL>(sm.key + pix0, key);
       store_flags<PPL>(sm.flag + pix0, fl);
     }
-  });
+  };
+  if constexpr (BOUND)
+    bound_event<PPL, W, CH, NT>(c, r, take);
+  else
+    extract_event<EX, PPL, W, CH, NT>(c, r, ev, sm.rows, &sm.start, xrow, sm.flag, take);
   if ((threadIdx.x & (kWave - 1)) == 0) sm.nlow_w[wave] = nlow;
   return ncand;
 }
@@ -1757,12 +1857,197 @@ __device__ __forceinline__ rta_hillas_rec given_image(const DevCam& c, TelSmem& 
   return small_image<NT>(sm, n, nlow, s, ((volatile unsigned long long*)sm.small.adj)[lane]);
 }
 
+// Neighbour peak windows of the pixels that can matter, after the bounds
+// (sm.key, sm.flag and the wavefronts' runs of flagged pixels hold those).
+// The mask of the bounds' flags contains the image's mask, and the image's
+// mask looks only at the flags of its pixels and of the neighbours they
+// list; those pixels, usually few more than the image, are asked, and all
+// other flags are cleared.  The traces of the asked pixels and of their
+// neighbours are staged in LDS, as many slices at once as fit (the whole
+// trace of 128 slices for 60 pixels): lanes on pixels, which share cache
+// lines within a slice.  (A wavefront per asked pixel with lanes on slices
+// took a line per lane and load, 130 us for an image of 33 pixels.)  Then a
+// lane has an asked pixel, each wavefront a part of the windows.  8000
+// events of the 1:3:6 mix: 1123 us with the full scan of every pixel (six
+// 8-byte LDS reads and some 50 vector instructions per pixel and four
+// slices), 600 us so, at 6.4 TB/s for the trace once and the asked pixels'
+// cache lines a second time (1.35 times the trace in all).  Returns false if more than kNbrAsk pixels are asked or more than kNbrStage traces
+// needed: every pixel is then scanned, from the start.  none: set when no
+// pixel is asked.
+template <int NT, int W>
+__device__ __forceinline__ bool nbr_windows(const DevCam& c, NbrSmem& nm, int ncand, const uint16_t* __restrict__ ev,
+                                            bool* none) {
+  TelSmem& sm = nm.tel;
+  constexpr int NW = NT / kWave;
+  const int np = c.n_pix_pad, T = c.n_samp, nw = (c.n_pix + 63) >> 6;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint16_t* cand = sm.list + wave * (kMaxPix / NW);
+  uint32_t* m32 = reinterpret_cast<uint32_t*>(sm.mbits);
+  auto each_neighbour = [](const int4& nv, auto&& fn) {
+    const int32_t nb2[3] = {nv.x, nv.y, nv.z};
+#pragma unroll
+    for (int k = 0; k < 6; ++k) fn(k, (k & 1) ? nb2[k >> 1] >> 16 : (int)(int16_t)nb2[k >> 1]);
+  };
+  auto list_mask = [&](int wbase, uint16_t* list) {  // mask pixels in order
+    for (int w = wave; w < nw; w += NW) {
+      const uint64_t bits = sm.mbits[w];
+      const int first = __builtin_amdgcn_readlane(wbase, __builtin_amdgcn_readfirstlane(w));
+      if ((bits >> lane) & 1ull) list[first + __popcll(bits & ((1ull << lane) - 1ull))] = (uint16_t)((w << 6) | lane);
+    }
+  };
+  __syncthreads();
+  for (int b = lane; b < ncand; b += kWave) {
+    const int i = cand[b];
+    const int4 nv = neighbour_row(c, i);
+    if (!passes(sm, sm.flag[i], nv)) continue;
+    atomicOr(&m32[i >> 5], 1u << (i & 31));
+    each_neighbour(nv, [&](int, int j) {
+      if (j >= 0 && (sm.flag[j] & 3u)) atomicOr(&m32[j >> 5], 1u << (j & 31));
+    });
+  }
+  __syncthreads();
+  int n;
+  const int abase = scan_phase(c.n_pix, sm, &n);
+  *none = n == 0;
+  if (n == 0) return true;
+  if (n > kNbrAsk) return false;
+  list_mask(abase, sm.ask);
+  for (int b = lane; b < ncand; b += kWave) {
+    const int i = cand[b];
+    if (!mask_bit(sm, i)) sm.flag[i] &= 4u;
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < n; j += NT) {
+    const int i = sm.ask[j];
+    sm.key[i] = 0u;
+    each_neighbour(neighbour_row(c, i), [&](int, int k) {
+      if (k >= 0) atomicOr(&m32[k >> 5], 1u << (k & 31));
+    });
+  }
+  __syncthreads();
+  int nu;
+  const int ubase = scan_phase(c.n_pix, sm, &nu);
+  if (nu > kNbrStage) return false;
+  list_mask(ubase, nm.px);
+  // Tc slices at once, rows of rw dwords (2 mod 4, so that the lanes of a
+  // store spread over the banks), row nu all zero for missing neighbours
+  int Tc = ((kXrow / (nu + 1)) & ~3) - 4;
+  Tc = min(Tc, (T + 3) & ~3);
+  const int rw = Tc / 2 + ((Tc & 4) ? 0 : 2);
+  uint32_t* xw = reinterpret_cast<uint32_t*>(nm.xrow);
+  for (int z = threadIdx.x; z < rw; z += NT) xw[nu * rw + z] = 0u;
+  const int starts = Tc - (W - 1);  // windows of a stage
+  for (int s0 = 0; s0 + W <= T; s0 += starts) {
+    __syncthreads();
+    const int slices = min(Tc, T - s0);
+    // 64 pixels of one slice per load; a wavefront's loads go in runs of 32
+    // that are in flight together
+    const int blocks = (nu + kWave - 1) / kWave;
+    constexpr int U = 24;
+    int u0 = 0, t = wave;
+    while (t >= slices) {  // fewer slices than wavefronts
+      t -= slices;
+      u0 += kWave;
+    }
+    while (u0 < blocks * kWave) {
+      uint16_t x[U];
+      int at[U];  // store position, -1: none
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int u = u0 + lane;
+        at[k] = u < nu ? u * rw * 2 + t : -1;
+        x[k] = ev[(size_t)(s0 + t) * np + nm.px[min(u, nu - 1)]];
+        t += NW;
+        while (t >= slices) {
+          t -= slices;
+          u0 += kWave;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+        if (at[k] >= 0) nm.xrow[at[k]] = x[k];
+    }
+    __syncthreads();
+    // this wavefront's windows: starts [a, b) of the stage
+    const int nwin = slices - (W - 1), part = ((nwin + NW - 1) / NW + 3) & ~3;
+    const int a = wave * part, b = min(a + part, nwin);
+    if (a < b)
+      for (int j = lane; j < n; j += kWave) {
+        const int i = sm.ask[j];
+        int off[6];
+        each_neighbour(neighbour_row(c, i),
+                       [&](int k, int m) { off[k] = (m >= 0 ? mask_slot(sm, m) : nu) * rw + (a >> 1); });
+        const us2 row_lo = {1, 0}, row_hi = {0, 1};
+        uint32_t y[7] = {0, 0, 0, 0, 0, 0, 0}, best = 0;  // y(t-3) .. y(t+3)
+        for (int t = a; t < b + W - 1; t += 4) {
+          y[0] = y[4]; y[1] = y[5]; y[2] = y[6];
+          y[3] = y[4] = y[5] = y[6] = 0;
+#pragma unroll
+          for (int k = 0; k < 6; ++k) {
+            // a 64-bit word, not a two-element vector: the packed dot of such
+            // a vector's second element has been seen compiled onto its first
+            const uint64_t v = *reinterpret_cast<const uint64_t*>(xw + off[k]);
+            const uint32_t v01 = (uint32_t)v, v23 = (uint32_t)(v >> 32);
+            off[k] += 2;
+            y[3] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v01), row_lo, y[3], false);
+            y[4] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v01), row_hi, y[4], false);
+            y[5] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_lo, y[5], false);
+            y[6] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_hi, y[6], false);
+          }
+#pragma unroll
+          for (int z = 0; z < 4; ++z) {
+            const int s = t + z - (W - 1);  // the window that ends with slice t + z
+            const uint32_t C = y[z] + y[z + 1] + y[z + 2] + y[z + 3];
+            if (s >= a && s < b) best = max(best, (C << 8) | (uint32_t)(255 - (s0 + s)));
+          }
+        }
+        atomicMax(&sm.key[i], best);
+      }
+  }
+  __syncthreads();
+  if (threadIdx.x < kMaxWords) sm.mbits[threadIdx.x] = 0ull;  // for the image's own mask
+  // four lanes per asked pixel take its window's samples on its gain
+  static_assert(W == 4, "one sample per lane of a quad");
+  for (int j0 = 0; j0 < n; j0 += NT / 4) {
+    const int j = j0 + ((int)threadIdx.x >> 2);
+    const int i = sm.ask[min(j, n - 1)];
+    const int g = (int)(sm.flag[i] >> 2), o = g * np + i, s = 255 - (int)(sm.key[i] & 255u);
+    const int32_t P = c.P256[o], tb = c.thr_bnd[o], tp = c.thr_pic[o];
+    uint32_t S = ev[((size_t)g * T + s + (threadIdx.x & 3)) * np + i];
+    S += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)S, 0xB1, 0xF, 0xF, false);
+    S += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)S, 0x4E, 0xF, 0xF, false);
+    if (j < n && (threadIdx.x & 3) == 0) {
+      const uint32_t key = (S << 8) | (uint32_t)(255 - s);
+      const int32_t d = key_to_d<W>(key, P);
+      sm.key[i] = key;
+      sm.flag[i] = (uint8_t)((uint32_t)(d >= tb) | ((uint32_t)(d >= tp) << 1) | ((uint32_t)g << 2));
+    }
+  }
+  __syncthreads();
+  return true;
+}
+
 // Calibration -> cleaning -> Hillas of one camera event; the threads of
 // wavefront 0 return the record.
 template <int EX, int PPL, int W, int CH, int NT>
 __device__ __forceinline__ rta_hillas_rec process_telescope(const DevCam& c, const uint16_t* __restrict__ ev,
-                                                            TelSmem& sm) {
-  const int ncand = extract_phase<EX, PPL, W, CH, NT>(c, ev, sm);
+                                                            uint8_t* raw) {
+  TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
+  uint16_t* xrow = nullptr;
+  if constexpr (EX == kExNeighbour) {
+    NbrSmem& nm = *reinterpret_cast<NbrSmem*>(raw);
+    xrow = nm.xrow;
+    if (!c.nbr_scan) {
+      const int ncand = extract_phase<EX, PPL, W, CH, NT, true>(c, ev, sm, xrow);
+      bool none;
+      if (nbr_windows<NT, W>(c, nm, ncand, ev, &none)) {
+        if (none) return empty_image(total_count<NT>(sm));
+        return fused_image<NT, W>(c, sm, ncand, ev);
+      }
+      __syncthreads();  // the wavefronts' runs and the mask words have been read
+    }
+  }
+  const int ncand = extract_phase<EX, PPL, W, CH, NT, false>(c, ev, sm, xrow);
   return fused_image<NT, W>(c, sm, ncand, ev);
 }
 
@@ -1776,8 +2061,9 @@ __device__ __forceinline__ void bad_record(rta_hillas_rec* out) {
 }
 
 // Waves per SIMD the register allocation must leave room for: the neighbour
-// peak's 256-thread workgroups fit four to a compute unit by their LDS, if
-// the registers allow it.  Elsewhere the compiler's own choice stands.
+// peak's 256-thread workgroups fit four to a compute unit by their LDS (37
+// KB), if the registers allow it; its full scan, bound by latency, loses 8 %
+// with three.  Elsewhere the compiler's own choice stands.
 template <int EX, int NT>
 constexpr int min_waves() {
   return EX == kExNeighbour && NT == 256 ? 4 : 1;
@@ -1794,6 +2080,7 @@ __global__ __launch_bounds__(NT) void k_calibrate(DevCam c, const uint16_t* __re
                                                   float* q, float* t) {
   __shared__ uint32_t rows[EX == kExGlobal ? NT / kWave * 256 : (EX == kExNeighbour ? kMaxPix : 1)];
   __shared__ __attribute__((aligned(16))) uint16_t xrow[EX == kExNeighbour ? kNbrRows * (kMaxPix + 8) : 8];
+  __shared__ __attribute__((aligned(8))) uint8_t low[EX == kExNeighbour ? kMaxPix : 8];
   __shared__ int32_t start;
   const int64_t e = blockIdx.x;
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
@@ -1831,7 +2118,7 @@ __global__ __launch_bounds__(NT) void k_calibrate(DevCam c, const uint16_t* __re
     }
     return;
   }
-  extract_event<EX, PPL, W, 2 * W, NT>(c, r, ev, rows, &start, xrow, [&](int pix0, const uint32_t (&key)[PPL],
+  extract_event<EX, PPL, W, 2 * W, NT>(c, r, ev, rows, &start, xrow, low, [&](int pix0, const uint32_t (&key)[PPL],
                                                                          uint32_t sw) {
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
@@ -1942,7 +2229,7 @@ __device__ __forceinline__ void classify_telescope(const FusedArgs& a, long long
 // Per-telescope body of the fused kernel: descriptor checks, then
 // calibration -> cleaning -> Hillas with all intermediates in LDS.
 template <int EX, int PPL, int W, int CH, int NT>
-__device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long tel, TelSmem& sm) {
+__device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long tel, uint8_t* raw) {
   const int ty = uniform_i32(a.tel_type[tel]);
   const long long off = uniform_i64(a.tel_trace_off[tel]);
   const uint32_t bad = tel_descriptor_status(ty, off, a.n_types, a.traces_len,
@@ -1958,7 +2245,7 @@ __device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long te
     }
     return;
   }
-  rta_hillas_rec r = process_telescope<EX, PPL, W, CH, NT>(a.cams[ty], uniform_ptr(a.traces + off), sm);
+  rta_hillas_rec r = process_telescope<EX, PPL, W, CH, NT>(a.cams[ty], uniform_ptr(a.traces + off), raw);
   if (a.classify && threadIdx.x < kWave) classify_telescope(a, tel, r);
   if (threadIdx.x == 0) a.out[tel] = r;
 }
@@ -1970,7 +2257,6 @@ __device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long te
 template <int EX, int PPL, int W, int CH, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_fused(FusedArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t raw[smem_bytes<EX>()];
-  TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
   __shared__ long long s_tel;
   for (;;) {
     if (threadIdx.x == 0) s_tel = (long long)atomicAdd(a.queue, 1ull);
@@ -1978,7 +2264,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const long long tel = uniform_i64(s_tel);
     __syncthreads();
     if (tel >= a.n_tel) return;
-    fused_telescope<EX, PPL, W, CH, NT>(a, tel, sm);
+    fused_telescope<EX, PPL, W, CH, NT>(a, tel, raw);
     __syncthreads();
   }
 }
@@ -1990,8 +2276,7 @@ template <int EX, int PPL, int W, int CH, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(min_waves<EX, NT>()))) void k_fused_grid(
     FusedArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t raw[smem_bytes<EX>()];
-  TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
-  fused_telescope<EX, PPL, W, CH, NT>(a, (long long)blockIdx.x, sm);
+  fused_telescope<EX, PPL, W, CH, NT>(a, (long long)blockIdx.x, raw);
 }
 
 // Array events: stereo direction from the telescope records and, when
