@@ -25,31 +25,26 @@
 
 namespace rta {
 using namespace mlpdev;
-constexpr int kRowsNT = 256;  // 4 wavefronts, 16 rows each
+constexpr int kRowsNT = 64;  // one wavefront, 16 rows
 
 namespace {
 
-// Standardised input tile of batch rows r0..r0+15 taken from data rows
-// rows[b] (clamped to [0, n_data)) of x [n_data][10].
-__device__ __forceinline__ bf16x4 gather_input_tile(const MlpDev& w, const float* x, const int64_t* rows,
-                                                    int64_t n_data, int B, int r0) {
-  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-  const int b = r0 + col;
-  int64_t d = 0;
-  if (b < B) d = min(max(rows[b], (int64_t)0), n_data - 1);
-  float v[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int f = 4 * grp + j;
-    v[j] = (b < B && f < kIn) ? (x[d * kIn + f] - w.mean[f]) / w.stdv[f] : 0.f;
-  }
-  return pack4(v[0], v[1], v[2], v[3]);
-}
-
 // Forward (+ loss, + backward to every layer's pre-activation gradient when
-// TRAIN) of 16-row tiles, one per wavefront.  rows != null: batch row b is
-// data row rows[b] of x / label / log10e (the batch gather done here
-// instead of in separate copies).
+// TRAIN) of 16-row tiles, a single-wavefront workgroup each: a batch of 4096
+// is 256 tiles, one per compute unit.  rows != null (TRAIN): batch row b is
+// data row rows[b] of x / label / log10e (the batch gather done here instead
+// of in separate copies).  A tile is one chain of dependent layers, bound by
+// latency: all weights, forward and backward, are loaded into registers at
+// the start (204 of them), while the row indices and then the rows arrive,
+// instead of layer by layer; the activations and gradients are transposed in
+// registers and stored 8 bytes per lane.  B = 4096: 15.4 -> 8.5 us.
+// Forward only, a wavefront takes tiles in turn and keeps the weights: 10^6
+// rows 284 -> 55 us.  (Training wavefronts that did so needed 292 registers:
+// 10 us at B = 4096.)
+struct BackFrag {
+  bf16x4 w4[4], w3[4][4], w2[4][4];
+};
+
 template <bool TRAIN>
 __global__ __launch_bounds__(kRowsNT) void k_mlp_rows(MlpDev w, const float* __restrict__ x,
                                                       const float* __restrict__ label,
@@ -57,100 +52,129 @@ __global__ __launch_bounds__(kRowsNT) void k_mlp_rows(MlpDev w, const float* __r
                                                       const int64_t* __restrict__ rows, int64_t n_data, int B,
                                                       int Bpad, float* __restrict__ out) {
   const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-  const int r0 = (blockIdx.x * (kRowsNT / 64) + (threadIdx.x >> 6)) * 16;
-  if (r0 >= Bpad) return;
-  const int b = r0 + col;
-  const bool valid = b < B;
-  const bf16x4 xin = rows ? gather_input_tile(w, x, rows, n_data, B, r0) : mlp_input_tile(w, x, B, r0);
-  const int64_t db = (rows && valid) ? min(max(rows[b], (int64_t)0), n_data - 1) : (int64_t)b;
-  bf16x4 h1[4], h2[4], h3[4];
-  const f32x4 o = mlp_forward_tile(w, xin, h1, h2, h3);
-  if (!TRAIN) {
-    if (grp == 0 && valid) {
-      out[(size_t)b * 2] = o[0];
-      out[(size_t)b * 2 + 1] = o[1];
+  // data row of this lane's batch row, asked for ahead of the weights, since
+  // the row's own loads wait for it
+  int64_t db = (int64_t)blockIdx.x * 16 + col;
+  if (TRAIN && rows && db < B) db = min(max(rows[db], (int64_t)0), n_data - 1);
+  MlpFrag net;
+  mlp_load(w, net);
+  BackFrag back;
+  if constexpr (TRAIN) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) back.w4[t] = load4(w.W4n, kOutPad, 16 * t + col, 4 * grp);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        back.w3[t][u] = load4(w.W3n, kHid, 16 * t + col, 16 * u + 4 * grp);
+        back.w2[t][u] = load4(w.W2n, kHid, 16 * t + col, 16 * u + 4 * grp);
+      }
+  }
+  float mean[4], stdv[4];
+  load_scale(w, grp, mean, stdv);
+  for (int64_t r0 = (int64_t)blockIdx.x * 16; r0 < Bpad; r0 += (int64_t)gridDim.x * 16) {
+    const int b = (int)r0 + col;
+    const bool valid = b < B;
+    float v[4], lab = 0.f, y = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int f = 4 * grp + j;
+      v[j] = (valid && f < kIn) ? (x[db * kIn + f] - mean[j]) / stdv[j] : 0.f;
     }
-    return;
-  }
-  // loss and output gradient (lanes of group 0 own the two outputs of row b)
-  float g0 = 0.f, g1 = 0.f;
-  if (grp == 0) {
-    float lrow = 0.f;
-    if (valid) {
-      const float z = o[0], e = o[1], lab = label[db], y = log10e[db];
-      const float m = lab > 0.5f ? 1.f : 0.f;
-      const float sig = 1.f / (1.f + expf(-z));
-      lrow = fmaxf(z, 0.f) - z * lab + log1pf(expf(-fabsf(z))) + m * (e - y) * (e - y);
-      g0 = (sig - lab) / (float)B;
-      g1 = 2.f * m * (e - y) / (float)B;
+    if (TRAIN && valid) {
+      lab = label[db];
+      y = log10e[db];
     }
-    w.loss_row[b] = lrow;
-  }
-  const bf16x4 g4 = pack4(g0, g1, 0.f, 0.f);
-  // store H^T and G4^T (feature-major) for the weight-gradient contraction
-  store4T(w.H0, Bpad, 4 * grp, b, xin);
+    if constexpr (!TRAIN) db = r0 + (int64_t)gridDim.x * 16 + col;  // (no row gather without training)
+    __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first layer
+    const bf16x4 xin = pack4(v[0], v[1], v[2], v[3]);
+    bf16x4 h1[4], h2[4], h3[4];
+    const f32x4 o = mlp_forward(net, xin, h1, h2, h3);
+    if (!TRAIN) {
+      if (grp == 0 && valid) {
+        out[(size_t)b * 2] = o[0];
+        out[(size_t)b * 2 + 1] = o[1];
+      }
+      continue;
+    }
+    // loss and output gradient (lanes of group 0 own the two outputs of row b)
+    float g0 = 0.f, g1 = 0.f;
+    if (grp == 0) {
+      float lrow = 0.f;
+      if (valid) {
+        const float z = o[0], e = o[1];
+        const float m = lab > 0.5f ? 1.f : 0.f;
+        const float sig = 1.f / (1.f + expf(-z));
+        lrow = fmaxf(z, 0.f) - z * lab + log1pf(expf(-fabsf(z))) + m * (e - y) * (e - y);
+        g0 = (sig - lab) / (float)B;
+        g1 = 2.f * m * (e - y) / (float)B;
+      }
+      w.loss_row[b] = lrow;
+    }
+    const bf16x4 g4 = pack4(g0, g1, 0.f, 0.f);
+    // dH3^T = W4 . G4^T, masked -> G3; then G2, G1
+    bf16x4 g3[4], g2[4], g1v[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    store4T(w.H1, Bpad, 16 * t + 4 * grp, b, h1[t]);
-    store4T(w.H2, Bpad, 16 * t + 4 * grp, b, h2[t]);
-    store4T(w.H3, Bpad, 16 * t + 4 * grp, b, h3[t]);
-  }
-  store4T(w.G4, Bpad, 4 * grp, b, g4);
-  // dH3^T = W4 . G4^T, masked -> G3; then G2, G1
-  bf16x4 g3[4], g2[4], g1v[4];
+    for (int t = 0; t < 4; ++t) {
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      g3[t] = mask_bf(mfma(back.w4[t], g4, zero), h3[t]);
+    }
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma(load4(w.W4n, kOutPad, 16 * t + col, 4 * grp), g4, acc);
-    g3[t] = mask_bf(acc, h3[t]);
-    store4T(w.G3, Bpad, 16 * t + 4 * grp, b, g3[t]);
-  }
+    for (int t = 0; t < 4; ++t) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int u = 0; u < 4; u += 2) acc = mfma2(back.w3[t][u], back.w3[t][u + 1], g3[u], g3[u + 1], acc);
+      g2[t] = mask_bf(acc, h2[t]);
+    }
 #pragma unroll
-    for (int u = 0; u < 4; u += 2)
-      acc = mfma2(load4(w.W3n, kHid, 16 * t + col, 16 * u + 4 * grp),
-                  load4(w.W3n, kHid, 16 * t + col, 16 * (u + 1) + 4 * grp), g3[u], g3[u + 1], acc);
-    g2[t] = mask_bf(acc, h2[t]);
-    store4T(w.G2, Bpad, 16 * t + 4 * grp, b, g2[t]);
-  }
+    for (int t = 0; t < 4; ++t) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int u = 0; u < 4; u += 2) acc = mfma2(back.w2[t][u], back.w2[t][u + 1], g2[u], g2[u + 1], acc);
+      g1v[t] = mask_bf(acc, h1[t]);
+    }
+    // H^T and G^T (feature-major) for the weight-gradient contraction
+    const int b0 = b & ~3;
+    store4T(w.H0, Bpad, 4 * grp, b0, xin);
+    store4T(w.G4, Bpad, 4 * grp, b0, g4);
 #pragma unroll
-    for (int u = 0; u < 4; u += 2)
-      acc = mfma2(load4(w.W2n, kHid, 16 * t + col, 16 * u + 4 * grp),
-                  load4(w.W2n, kHid, 16 * t + col, 16 * (u + 1) + 4 * grp), g2[u], g2[u + 1], acc);
-    g1v[t] = mask_bf(acc, h1[t]);
-    store4T(w.G1, Bpad, 16 * t + 4 * grp, b, g1v[t]);
+    for (int t = 0; t < 4; ++t) {
+      store4T(w.H1, Bpad, 16 * t + 4 * grp, b0, h1[t]);
+      store4T(w.H2, Bpad, 16 * t + 4 * grp, b0, h2[t]);
+      store4T(w.H3, Bpad, 16 * t + 4 * grp, b0, h3[t]);
+      store4T(w.G3, Bpad, 16 * t + 4 * grp, b0, g3[t]);
+      store4T(w.G2, Bpad, 16 * t + 4 * grp, b0, g2[t]);
+      store4T(w.G1, Bpad, 16 * t + 4 * grp, b0, g1v[t]);
+    }
+    break;  // one tile per wavefront
   }
 }
 
 // Weight / bias gradients and the loss.  The batch contraction of each 16x16
-// weight tile (40) and bias vector (4) is cut into kGradSplit slices of
+// weight tile (40) and block of 16 biases (13) is cut into kGradSplit slices of
 // consecutive 16-row blocks, one wavefront per (tile, slice), each writing
 // its partial sums to gpart[slice]; a last wavefront sums the loss.  The
 // slices are added in slice order by grad_sum (fixed order: the gradient is
 // reproducible).  One long contraction per tile would leave the chip nearly
-// idle and every step waiting on the previous load.
-constexpr int kGradTiles = 44;
+// idle and every step waiting on the previous load.  A slice of up to 16
+// blocks (a batch of 4096) has all its loads in flight at once, and the loss
+// 32 rows per lane: 7.2 -> 5.7 us, two latencies and the launch.
+constexpr int kGradTiles = 53;
 constexpr int kGradBlocks = kGradTiles * kGradSplit + 1;
 
 __global__ __launch_bounds__(64) void k_mlp_grad(MlpDev w, int B, int Bpad, float* __restrict__ loss_out) {
   const int lane = threadIdx.x, col = lane & 15, grp = lane >> 4;
   if (blockIdx.x == kGradTiles * kGradSplit) {
-    // 16 loads in flight per step, added in row order
+    // 32 loads in flight per step, added in row order
     float s = 0.f;
-    int r = lane;
-    for (; r + 64 * 15 < B; r += 64 * 16) {
-      float v[16];
+    for (int r = lane; r < B; r += 64 * 32) {
+      float v[32];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = w.loss_row[r + 64 * u];
+      for (int u = 0; u < 32; ++u) v[u] = r + 64 * u < B ? w.loss_row[r + 64 * u] : 0.f;
 #pragma unroll
-      for (int u = 0; u < 16; ++u) s += v[u];
+      for (int u = 0; u < 32; ++u)
+        if (r + 64 * u < B) s += v[u];
     }
-    for (; r < B; r += 64) s += w.loss_row[r];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
     if (lane == 0) {
@@ -164,61 +188,43 @@ __global__ __launch_bounds__(64) void k_mlp_grad(MlpDev w, int B, int Bpad, floa
   const int nk = Bpad / 16, per = (nk + kGradSplit - 1) / kGradSplit;
   const int k0 = min(nk, sl * per), k1 = min(nk, k0 + per);
   float* __restrict__ part = w.gpart + (size_t)sl * kNParams;
-  if (wv < 40) {
-    // tile -> (layer, input chunk, output chunk)
-    const uint16_t *H, *G;
-    int in0, out0, in_dim, out_dim, off;
-    if (wv < 4) { H = w.H0; G = w.G1; in0 = 0; out0 = 16 * wv; in_dim = kIn; out_dim = kHid; off = kOffW1; }
-    else if (wv < 20) { const int t = wv - 4; H = w.H1; G = w.G2; in0 = 16 * (t / 4); out0 = 16 * (t % 4); in_dim = kHid; out_dim = kHid; off = kOffW2; }
-    else if (wv < 36) { const int t = wv - 20; H = w.H2; G = w.G3; in0 = 16 * (t / 4); out0 = 16 * (t % 4); in_dim = kHid; out_dim = kHid; off = kOffW3; }
-    else { H = w.H3; G = w.G4; in0 = 16 * (wv - 36); out0 = 0; in_dim = kHid; out_dim = kOut; off = kOffW4; }
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    int k = k0;
-    for (; k + 4 <= k1; k += 4) {  // four 16-row blocks loaded before their MFMAs
-      bf16x4 a[4], b[4];
+  // tile -> (layer, input chunk, output chunk); biases: a row of ones as input
+  const uint16_t *H = nullptr, *G;
+  int in0 = 0, out0, in_dim = 1, out_dim, off;
+  if (wv < 4) { H = w.H0; G = w.G1; out0 = 16 * wv; in_dim = kIn; out_dim = kHid; off = kOffW1; }
+  else if (wv < 20) { const int t = wv - 4; H = w.H1; G = w.G2; in0 = 16 * (t / 4); out0 = 16 * (t % 4); in_dim = kHid; out_dim = kHid; off = kOffW2; }
+  else if (wv < 36) { const int t = wv - 20; H = w.H2; G = w.G3; in0 = 16 * (t / 4); out0 = 16 * (t % 4); in_dim = kHid; out_dim = kHid; off = kOffW3; }
+  else if (wv < 40) { H = w.H3; G = w.G4; in0 = 16 * (wv - 36); out0 = 0; in_dim = kHid; out_dim = kOut; off = kOffW4; }
+  else if (wv < 52) {
+    const int l = (wv - 40) / 4;
+    G = l == 0 ? w.G1 : l == 1 ? w.G2 : w.G3;
+    out0 = 16 * (wv & 3); out_dim = kHid; off = l == 0 ? kOffB1 : l == 1 ? kOffB2 : kOffB3;
+  } else { G = w.G4; out0 = 0; out_dim = kOut; off = kOffB4; }
+  bf16x4 ones;
+  ones[0] = ones[1] = ones[2] = ones[3] = (short)0x3F80;  // bf16(1.0)
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 16;  // 16-row blocks loaded before their MFMAs
+  for (int k = k0; k < k1; k += U) {
+    bf16x4 a[U], b[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = load4(H, Bpad, in0 + col, 16 * (k + u) + 4 * grp);
+    for (int u = 0; u < U; ++u)
+      if (k + u < k1) {
+        a[u] = H ? load4(H, Bpad, in0 + col, 16 * (k + u) + 4 * grp) : ones;
         b[u] = load4(G, Bpad, out0 + col, 16 * (k + u) + 4 * grp);
       }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < 4; u += 2) acc = mfma2(a[u], a[u + 1], b[u], b[u + 1], acc);
+    for (int u = 0; u < U; u += 2) {
+      if (k + u + 1 < k1)
+        acc = mfma2(a[u], a[u + 1], b[u], b[u + 1], acc);
+      else if (k + u < k1)
+        acc = mfma(a[u], b[u], acc);
     }
-    for (; k + 2 <= k1; k += 2)
-      acc = mfma2(load4(H, Bpad, in0 + col, 16 * k + 4 * grp), load4(H, Bpad, in0 + col, 16 * (k + 1) + 4 * grp),
-                  load4(G, Bpad, out0 + col, 16 * k + 4 * grp), load4(G, Bpad, out0 + col, 16 * (k + 1) + 4 * grp),
-                  acc);
-    if (k < k1)
-      acc = mfma(load4(H, Bpad, in0 + col, 16 * k + 4 * grp), load4(G, Bpad, out0 + col, 16 * k + 4 * grp), acc);
+  }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = in0 + 4 * grp + i, n = out0 + col;
-      if (m < in_dim && n < out_dim) part[off + m * out_dim + n] = acc[i];
-    }
-  } else {
-    const int l = wv - 40;  // bias of layer l+1
-    const uint16_t* G = l == 0 ? w.G1 : l == 1 ? w.G2 : l == 2 ? w.G3 : w.G4;
-    const int nchunk = l == 3 ? 1 : 4, dim = l == 3 ? kOut : kHid;
-    const int off = l == 0 ? kOffB1 : l == 1 ? kOffB2 : l == 2 ? kOffB3 : kOffB4;
-    bf16x4 ones;
-    ones[0] = ones[1] = ones[2] = ones[3] = (short)0x3F80;  // bf16(1.0)
-    for (int c = 0; c < nchunk; ++c) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      int k = k0;
-      for (; k + 4 <= k1; k += 4) {
-        bf16x4 b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) b[u] = load4(G, Bpad, 16 * c + col, 16 * (k + u) + 4 * grp);
-#pragma unroll
-        for (int u = 0; u < 4; u += 2) acc = mfma2(ones, ones, b[u], b[u + 1], acc);
-      }
-      for (; k + 2 <= k1; k += 2)
-        acc = mfma2(ones, ones, load4(G, Bpad, 16 * c + col, 16 * k + 4 * grp),
-                    load4(G, Bpad, 16 * c + col, 16 * (k + 1) + 4 * grp), acc);
-      if (k < k1) acc = mfma(ones, load4(G, Bpad, 16 * c + col, 16 * k + 4 * grp), acc);
-      const int n = 16 * c + col;
-      if (grp == 0 && n < dim) part[off + n] = acc[0];
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int m = in0 + 4 * grp + i, n = out0 + col;
+    if (m < in_dim && n < out_dim) part[off + m * out_dim + n] = acc[i];
   }
 }
 
@@ -295,8 +301,9 @@ hipError_t launch_mlp_rows(const MlpDev& w, const float* x, const float* label, 
 hipError_t launch_mlp_rows_gather(const MlpDev& w, const float* x, const float* label, const float* log10e,
                                   const int64_t* rows, int64_t n_data, int B, int Bpad, float* out, bool train,
                                   hipStream_t st) {
-  const int tiles = Bpad / 16;
-  const int grid = (tiles + 3) / 4;
+  // forward: three wavefronts per SIMD of 256 compute units, as the registers
+  // allow, then tiles in turn
+  const int grid = train || Bpad / 16 < 12 * 256 ? Bpad / 16 : 12 * 256;
   if (train)
     hipLaunchKernelGGL(k_mlp_rows<true>, dim3(grid), dim3(kRowsNT), 0, st, w, x, label, log10e, rows, n_data, B,
                        Bpad, out);

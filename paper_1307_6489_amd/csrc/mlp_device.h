@@ -79,11 +79,21 @@ __device__ __forceinline__ bf16x4 mask_bf(f32x4 g, bf16x4 h) {
   return pack4(h[0] ? g[0] : 0.f, h[1] ? g[1] : 0.f, h[2] ? g[2] : 0.f, h[3] ? g[3] : 0.f);
 }
 
-__device__ __forceinline__ void store4T(uint16_t* MT, int ldb, int f0, int b, bf16x4 v) {
-  MT[(size_t)(f0 + 0) * ldb + b] = (uint16_t)v[0];
-  MT[(size_t)(f0 + 1) * ldb + b] = (uint16_t)v[1];
-  MT[(size_t)(f0 + 2) * ldb + b] = (uint16_t)v[2];
-  MT[(size_t)(f0 + 3) * ldb + b] = (uint16_t)v[3];
+// Stores a fragment (lane: row b of the batch, features f0 .. f0 + 3)
+// feature-major: the four lanes of a quad exchange halfwords until lane j has
+// feature f0 + j of the quad's four rows, one 8-byte store instead of four
+// 2-byte ones.  b0: the quad's first row.
+__device__ __forceinline__ void store4T(uint16_t* MT, int ldb, int f0, int b0, bf16x4 v) {
+  const int j = threadIdx.x & 3;
+  const u32x2 d = __builtin_bit_cast(u32x2, v);
+  // pairs of rows: even lanes keep features 0 and 2 of two rows, odd 1 and 3
+  const uint32_t p0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d[0], 0xB1, 0xF, 0xF, false);  // lane ^ 1
+  const uint32_t p1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d[1], 0xB1, 0xF, 0xF, false);
+  const uint32_t sel = (j & 1) ? 0x03020706u : 0x05040100u;  // (partner high, own high) or (own low, partner low)
+  const uint32_t a0 = __builtin_amdgcn_perm(p0, d[0], sel), a1 = __builtin_amdgcn_perm(p1, d[1], sel);
+  // four rows: lanes 0, 1 keep a0, lanes 2, 3 a1
+  const uint32_t r = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(j < 2 ? a1 : a0), 0x4E, 0xF, 0xF, false);
+  *reinterpret_cast<u32x2*>(MT + (size_t)(f0 + j) * ldb + b0) = j < 2 ? u32x2{a0, r} : u32x2{r, a1};
 }
 
 // A wavefront's share of the network's weights: the A-operand fragments of
