@@ -922,18 +922,25 @@ rta_status rta_sam_create(const rta_sam_params* p, rta_sam** out) {
   for (int k = 0; k < p->n_scales; ++k)
     if (p->scales[k] < 1 || p->scales[k] > p->n_bins) return fail(RTA_E_SHAPE, "scale must be in [1, n_bins]");
   // disc and ring offsets, classified in FP64 from the float radii
-  std::vector<int32_t> offs;
+  std::vector<int32_t> offs, ring, deltas;
   const double on2 = (double)p->r_on * p->r_on, in2 = (double)p->r_in * p->r_in, out2 = (double)p->r_out * p->r_out;
   const int reach = (int)std::ceil(p->r_out);
+  int32_t widest = 0;
   for (int dy = -reach; dy <= reach; ++dy)
     for (int dx = -reach; dx <= reach; ++dx) {
       const double d2 = (double)(dx * dx + dy * dy);
       const int kind = d2 <= on2 ? 1 : (d2 > in2 && d2 <= out2 ? 2 : 0);
-      if (kind) offs.push_back((dx + 128) | ((dy + 128) << 8) | (kind << 16));
+      if (!kind) continue;
+      (kind == 1 ? offs : ring).push_back((dx + 128) | ((dy + 128) << 8));
+      widest = std::max(widest, std::max(std::abs(dx), std::abs(dy)));
     }
+  const int32_t n_disc = (int32_t)offs.size();
+  offs.insert(offs.end(), ring.begin(), ring.end());
+  for (int32_t o : offs) deltas.push_back((((o >> 8) & 0xFF) - 128) * (p->grid + 2 * widest) + (o & 0xFF) - 128);
   const size_t G2 = (size_t)p->grid * p->grid;
   const size_t oC = 0, oW = round256((size_t)p->n_bins * G2 * 4), oO = oW + round256((size_t)p->n_scales * G2 * 4);
-  const size_t total = oO + round256(offs.size() * 4);
+  const size_t oD = oO + round256(offs.size() * 4), oE = oD + round256(deltas.size() * 4);
+  const size_t total = oE + round256(G2 * 8);
   rta_sam* sam = new (std::nothrow) rta_sam();
   if (!sam) return fail(RTA_E_NOMEM, "host allocation failed");
   if (hipGetDevice(&sam->device) != hipSuccess || hipMalloc(&sam->dmem, total) != hipSuccess) {
@@ -941,7 +948,8 @@ rta_status rta_sam_create(const rta_sam_params* p, rta_sam** out) {
     return fail(RTA_E_NOMEM, "device allocation for the monitor failed");
   }
   uint8_t* base = static_cast<uint8_t*>(sam->dmem);
-  if (hipMemcpy(base + oO, offs.data(), offs.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMemcpy(base + oO, offs.data(), offs.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(base + oD, deltas.data(), deltas.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(sam->dmem);
     delete sam;
     return fail(RTA_E_HIP, "copy of the offset table failed");
@@ -957,11 +965,16 @@ rta_status rta_sam_create(const rta_sam_params* p, rta_sam** out) {
   d.gamma_cut = p->gamma_cut;
   d.sigma_alert = p->sigma_alert;
   d.r_on2 = (float)on2;
+  d.reach = widest;
+  d.n_disc = n_disc;
   for (int k = 0; k < RTA_SAM_MAX_SCALES; ++k) d.scales[k] = k < p->n_scales ? p->scales[k] : 1;
   d.counts = reinterpret_cast<int32_t*>(base + oC);
   d.win = reinterpret_cast<int32_t*>(base + oW);
   d.offs = reinterpret_cast<const int32_t*>(base + oO);
-  if (rta::launch_sam_clear(d, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+  d.deltas = reinterpret_cast<const int32_t*>(base + oD);
+  d.cells = reinterpret_cast<int32_t*>(base + oE);
+  if (rta::launch_sam_clear(d, nullptr) != hipSuccess || rta::launch_sam_cells(d, nullptr) != hipSuccess ||
+      hipDeviceSynchronize() != hipSuccess) {
     (void)hipFree(sam->dmem);
     delete sam;
     return fail(RTA_E_HIP, "clearing the counts failed");

@@ -117,10 +117,14 @@ struct SamDev {
   int32_t grid, n_bins, n_scales, n_offs;
   double t0, bin_s;
   float cell, gamma_cut, sigma_alert, r_on2;
+  int32_t reach;        // largest offset in x or y
+  int32_t n_disc;       // offsets of the disc, ahead of the ring's
   int32_t scales[RTA_SAM_MAX_SCALES];
-  int32_t* counts;      // [n_bins][grid][grid]
-  int32_t* win;         // [n_scales][grid][grid] window sums
-  const int32_t* offs;  // [n_offs] disc / ring offsets: (dx + 128) | (dy + 128) << 8 | kind << 16 (1 on, 2 off)
+  int32_t* counts;        // [n_bins][grid][grid]
+  int32_t* win;           // [n_scales][grid][grid] window sums
+  const int32_t* offs;    // [n_offs] disc, then ring offsets: (dx + 128) | (dy + 128) << 8
+  const int32_t* deltas;  // [n_offs] the same as dy * (grid + 2 reach) + dx
+  int32_t* cells;         // [grid][grid][2] disc and ring cells inside the grid
 };
 
 struct EventArgs {
@@ -170,6 +174,7 @@ hipError_t launch_health(const DevCam& c, const uint16_t* traces, int64_t n_evt,
                          uint64_t* part, uint64_t* acc, rta_pixel_health* pix, rta_camera_health* out,
                          hipStream_t st);
 hipError_t launch_sam_clear(const SamDev& d, hipStream_t st);
+hipError_t launch_sam_cells(const SamDev& d, hipStream_t st);
 hipError_t launch_sam_fill(const SamDev& d, const rta_event_rec* evt, const double* t, int64_t n, hipStream_t st);
 hipError_t launch_sam_search(const SamDev& d, int end_bin, double* sig, int32_t* n_on, int32_t* n_off,
                              rta_sam_alert* alerts, int max_alerts, int32_t* n_alerts, hipStream_t st);
