@@ -20,8 +20,8 @@ struct rta_camera {
   void* dmem = nullptr;
   rta_camera_info info{};
   int device = 0;
-  uint64_t* health_acc = nullptr;   // [3][G][Npad] health totals (s1, s2, n_sat), inside dmem
-  uint64_t* health_part = nullptr;  // [kHealthParts][3][G][Npad] per-workgroup partial sums, inside dmem
+  uint64_t* health_acc = nullptr;   // [2][G][Npad] health rms (bits) and flags, inside dmem
+  uint64_t* health_part = nullptr;  // [kHealthParts / G][3][G][Npad] per-workgroup partial sums, inside dmem
   double max_a = 0.0;                // largest adc_per_pe of the camera (threshold range checks)
 };
 
@@ -412,8 +412,8 @@ rta_status rta_camera_create(const rta_camera_desc* d, rta_camera** out) {
   const size_t oB = oN + round256(nb.size() * 2), oC = oB + round256(border.size());
   const size_t oL = oC + round256(crc.size() * 2), oLP = oL + round256(lat.size() * 2);
   const size_t oH = oLP + round256(lpos.size() * 2);
-  const size_t oHP = oH + round256((size_t)3 * G * Np * 8);
-  const size_t total = oHP + round256((size_t)rta::kHealthParts * 3 * G * Np * 8);
+  const size_t oHP = oH + round256((size_t)2 * G * Np * 8);
+  const size_t total = oHP + round256((size_t)rta::kHealthParts * 3 * Np * 8);
   // tables are copied from the host; the health scratch after them is
   // written by the health kernels before it is read
   std::vector<uint8_t> host(oH, 0);
