@@ -3,9 +3,10 @@
 // The real-time analysis receives camera events as a byte stream formatted
 // like space telemetry source packets (paper, Section 5); the packet layout
 // is defined in rta.h.  One workgroup decodes one packet: the header is read
-// by every lane (uniform), then lane l owns bytes [16 l, 16 l + 16) of every
-// sample row (G*T rows of 2N bytes, N <= 2048 so a row has at most 256
-// pieces).  Per row the lane
+// by every lane (uniform), then lane l of a slot of 256 lanes owns bytes
+// [16 l, 16 l + 16) of sample rows (G*T rows of 2N bytes, N <= 2048 so a row
+// has at most 256 pieces); with S slots in the workgroup, slot s takes the
+// blocks of R rows s, s + S, ...  Per row the lane
 //   * loads its 16 bytes (two aligned loads and a funnel shift: packets are
 //     only 2-byte aligned in the stream),
 //   * swaps the big-endian samples to little-endian and stores them as one
@@ -14,10 +15,11 @@
 // CRC over GF(2): the register after a message M from register 0 is
 // crc0(M) = M(x) x^16 mod P, and crc0(A || B) = crc0(A) x^(8|B|) + crc0(B).
 // The lane's pieces recur every 2N bytes, so its share is the Horner sum
-// h <- h*K + crc0(piece) with K = x^(16N) (a table product), times x^(8 a_l)
-// for the a_l bytes after its piece in the last row.  The shares, the
-// header's crc0 times x^(8*body) and the initial register's 0xFFFF *
-// x^(8*(32+body)) XOR to the packet's CRC.
+// h <- h*K + crc0(piece) with K = x^(16N) (a table product; from one block to
+// the slot's next a power of K, another table), times x^(8 a_l) for the a_l
+// bytes after its piece in its last row and the power of K for the rows after
+// that one.  The shares, the header's crc0 times x^(8*body) and the initial
+// register's 0xFFFF * x^(8*(32+body)) XOR to the packet's CRC.
 #include "rta_internal.h"
 
 namespace rta {
@@ -57,22 +59,44 @@ __device__ __forceinline__ uint32_t wave_xor_last(uint32_t v) {
 
 // Sixteen stream bytes from byte offset off (2-byte aligned) of the buffer:
 // two aligned loads and a funnel shift by 0 or 2 bytes.
-__device__ __forceinline__ void load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t (&w)[4]) {
-  const uint32_t a = off & ~3u, sh = (off & 3u) * 8u;
-  const u32x4 d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)a, 0, 0);
-  const uint32_t e = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(a + 16u), 0, 0);
+__device__ __forceinline__ void load_piece(__amdgpu_buffer_rsrc_t r, uint32_t off, u32x4& d, uint32_t& e) {
+  const uint32_t a = off & ~3u;
+  d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)a, 0, 0);
+  e = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(a + 16u), 0, 0);
+}
+
+__device__ __forceinline__ void shift_piece(const u32x4& d, uint32_t e, uint32_t off, uint32_t (&w)[4]) {
+  const uint32_t sh = (off & 3u) * 8u;
   w[0] = __builtin_amdgcn_alignbit(d[1], d[0], sh);
   w[1] = __builtin_amdgcn_alignbit(d[2], d[1], sh);
   w[2] = __builtin_amdgcn_alignbit(d[3], d[2], sh);
   w[3] = __builtin_amdgcn_alignbit(e, d[3], sh);
 }
 
+__device__ __forceinline__ void load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t (&w)[4]) {
+  u32x4 d;
+  uint32_t e;
+  load_piece(r, off, d, e);
+  shift_piece(d, e, off, w);
+}
+
 __device__ __forceinline__ uint32_t byte_of(const uint32_t (&w)[8], int i) { return (w[i >> 2] >> ((i & 3) * 8)) & 0xFFu; }
 
-__global__ __launch_bounds__(kDecodeNT) void k_decode_packets(DecodeArgs a) {
-  __shared__ uint16_t T0[256], T1[256], KL[256], KH[256];
-  __shared__ uint32_t share[kDecodeNT / kWave];
-  const int lane = threadIdx.x;
+// Bound by the copy it makes, at most 4.8 TB/s read and written; a row's loads
+// and the CRC's table lookups in LDS hide behind each other.  2000 packets of
+// three cameras (1.43 GB in, the same out) take 598 us (4.8 TB/s), 691 with one
+// slot per packet, four rows loaded and then reduced: the large packets were
+// the last to finish, and 2000 streams at once are more than the memory takes
+// well.  One packet of 2 x 128 x 2048 samples takes 55 us in four slots, 62 in
+// two and 94 in one.
+template <int S, int R>
+__global__ __launch_bounds__(kDecodeNT * S) void k_decode_packets(DecodeArgs a) {
+  constexpr int F = S == kDecodeForms[0].slots ? 0 : 1;
+  static_assert(S == 1 || (S == kDecodeForms[F].slots && R == kDecodeForms[F].rows), "no tables for this form");
+  __shared__ uint16_t T0[256], T1[256], KL[256], KH[256], JL[S > 1 ? 256 : 1], JH[S > 1 ? 256 : 1];
+  __shared__ uint32_t share[S * kDecodeNT / kWave];
+  const int lane = (int)threadIdx.x % kDecodeNT;
+  const uint32_t slot_no = S > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kDecodeNT) : 0u;
   const int64_t p = blockIdx.x;
   // CRC byte tables from the polynomial: T0[i] = i x^16 mod P, T1[i] = i x^24 mod P
   {
@@ -139,6 +163,10 @@ __global__ __launch_bounds__(kDecodeNT) void k_decode_packets(DecodeArgs a) {
     const DevCam& c = a.cams[ty];
     KL[lane] = c.crc_tab[lane];
     KH[lane] = c.crc_tab[256 + lane];
+    if constexpr (S > 1) {
+      JL[lane] = c.crc_tab[crc_jump(F) + lane];
+      JH[lane] = c.crc_tab[crc_jump(F) + 256 + lane];
+    }
     __syncthreads();
     const uint32_t row = 2u * N, rows = T * G, np = (uint32_t)c.n_pix_pad;
     const uint32_t lo = 16u * (uint32_t)lane;
@@ -146,14 +174,24 @@ __global__ __launch_bounds__(kDecodeNT) void k_decode_packets(DecodeArgs a) {
     const int nb = act ? (int)min(16u, row - lo) : 0;  // bytes of this lane's piece (even)
     uint16_t* dst = a.pool + slot + 8 * lane;
     uint32_t h = 0;
-    uint32_t in = o0 + 32u + lo;
-    // four rows in flight per lane: loads past the packet's last row read the
-    // next packet or the padding and are ignored
-    constexpr int R = 4;
-    for (uint32_t k0 = 0; k0 < rows; k0 += R, in += R * row) {
+    // R rows in flight per lane while the R before them are reduced: loads
+    // past the packet's last row read the next packet or the padding and are
+    // ignored
+    uint32_t in = o0 + 32u + lo + slot_no * R * row;
+    u32x4 nd[R];
+    uint32_t ne[R];
+    auto load_rows = [&](uint32_t from) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) load_piece(r, from + (uint32_t)j * row, nd[j], ne[j]);
+    };
+    // a wavefront whose pieces all lie beyond the row has none to take
+    const uint32_t end = __ballot(act) ? rows : 0u;
+    if (slot_no * R < end) load_rows(in);
+    for (uint32_t k0 = slot_no * R; k0 < end; k0 += S * R, in += S * R * row) {
       uint32_t w[R][4];
 #pragma unroll
-      for (int j = 0; j < R; ++j) load16(r, in + (uint32_t)j * row, w[j]);
+      for (int j = 0; j < R; ++j) shift_piece(nd[j], ne[j], in + (uint32_t)j * row, w[j]);
+      if (k0 + S * R < end) load_rows(in + S * R * row);
       // CRC shares of the R pieces, two bytes (one sample) per step, the R
       // independent lookup chains interleaved; whole pieces take the
       // branch-free path, only the last lane of a row can hold fewer bytes
@@ -186,7 +224,9 @@ __global__ __launch_bounds__(kDecodeNT) void k_decode_packets(DecodeArgs a) {
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         if (k0 + j >= rows) continue;
-        h = (uint32_t)KH[h >> 8] ^ (uint32_t)KL[h & 0xFFu] ^ cc[j];
+        h = (S > 1 && j == 0 ? (uint32_t)JH[h >> 8] ^ (uint32_t)JL[h & 0xFFu]
+                             : (uint32_t)KH[h >> 8] ^ (uint32_t)KL[h & 0xFFu]) ^
+            cc[j];
         // big-endian samples -> little-endian, zero beyond the row
         u32x4 v;
 #pragma unroll
@@ -197,24 +237,25 @@ __global__ __launch_bounds__(kDecodeNT) void k_decode_packets(DecodeArgs a) {
         if (act) *reinterpret_cast<u32x4*>(dst + (size_t)(k0 + j) * np) = v;
       }
     }
+    if constexpr (S > 1) h = gf_mul_dev(h, c.crc_tab[crc_after(F) + (int)slot_no]);
     uint32_t share_l = act ? gf_mul_dev(h, c.crc_tab[512 + lane]) : 0u;
     share_l = wave_xor_last(share_l);
-    if ((lane & (kWave - 1)) == kWave - 1) share[lane / kWave] = share_l;
+    if ((lane & (kWave - 1)) == kWave - 1) share[threadIdx.x / kWave] = share_l;
     __syncthreads();
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
       uint32_t hc = 0;
 #pragma unroll
       for (int i = 0; i < 32; i += 2) hc = (uint32_t)T1[(hc >> 8) ^ g8(i)] ^ (uint32_t)T0[(hc & 0xFFu) ^ g8(i + 1)];
       crc_calc = gf_mul_dev(hc, c.crc_tab[768]) ^ c.crc_tab[769];
 #pragma unroll
-      for (int w = 0; w < kDecodeNT / kWave; ++w) crc_calc ^= share[w];
+      for (int w = 0; w < S * kDecodeNT / kWave; ++w) crc_calc ^= share[w];
       uint32_t t2[4];
       load16(r, o0 + 32u + (uint32_t)body, t2);
       crc_stored = ((t2[0] & 0xFFu) << 8) | ((t2[0] >> 8) & 0xFFu);
       if (crc_calc != crc_stored) flags |= RTA_PKT_CRC_BAD;
     }
   }
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     if (flags) {
       a.tel_type[p] = -1;
       atomicOr(a.status, RTA_STATUS_BAD_PACKET);
@@ -238,8 +279,23 @@ __global__ __launch_bounds__(kDecodeNT) void k_decode_packets(DecodeArgs a) {
 
 }  // namespace
 
-hipError_t launch_decode(const DecodeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_decode_packets, dim3((unsigned)a.n_pkt), dim3(kDecodeNT), 0, st, a);
+// Slots per packet.  With at most a packet per CU, four: a packet is a chain
+// of loads, and its CU is its own (250 packets of 2 x 30 x 1855 samples 28 us,
+// one slot 41).  Up to two per CU, two (500 of 2 x 30 x 400: 22 us, one slot
+// 32, four 34).  Beyond, by the mean packet: tables and header are a cost per
+// lane and a serial phase of few workgroups, so small packets take one slot
+// (4000 of 48 KB: 109 us, two 126), from 80 KB two (4000 of 111 KB: 178 us, one
+// 186, four 224), from 640 KB four, which also leaves fewer streams open (2000
+// of 715 KB: 598 us, two 668, one 707; at 445 KB two are ahead, 279 to 301).
+hipError_t launch_decode(const DecodeArgs& a, int n_cu, hipStream_t st) {
+  const int64_t mean = a.n_bytes / a.n_pkt;
+  const dim3 grid((unsigned)a.n_pkt);
+  if (a.n_pkt <= n_cu || mean >= 640 * 1024)
+    hipLaunchKernelGGL((k_decode_packets<4, 2>), grid, dim3(kDecodeNT * 4), 0, st, a);
+  else if (a.n_pkt <= 2 * n_cu || mean >= 80 * 1024)
+    hipLaunchKernelGGL((k_decode_packets<2, 4>), grid, dim3(kDecodeNT * 2), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_decode_packets<1, 4>), grid, dim3(kDecodeNT), 0, st, a);
   return hipGetLastError();
 }
 

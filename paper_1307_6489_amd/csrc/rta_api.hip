@@ -120,6 +120,20 @@ void crc_tables(int N, int T, int G, uint16_t* t) {
   }
   t[768] = (uint16_t)gf_pow8(body);
   t[769] = (uint16_t)gf_mul(0xFFFFu, gf_pow8(32 + body));
+  const int rows = T * G;
+  for (int f = 0; f < 2; ++f) {
+    const int S = rta::kDecodeForms[f].slots, B = rta::kDecodeForms[f].rows, blocks = (rows + B - 1) / B;
+    for (int s = 0; s < S; ++s) {
+      const int last = (blocks - 1 - s) / S * S + s;  // the slot's last block, if it has any
+      const int after = s < blocks ? rows - std::min(last * B + B, rows) : 0;
+      t[rta::crc_after(f) + s] = (uint16_t)gf_pow8(row * (uint64_t)after);
+    }
+    const uint32_t J = gf_pow8(row * (uint64_t)((S - 1) * B + 1));
+    for (uint32_t i = 0; i < 256; ++i) {
+      t[rta::crc_jump(f) + i] = (uint16_t)gf_mul(i, J);
+      t[rta::crc_jump(f) + 256 + i] = (uint16_t)gf_mul(i << 8, J);
+    }
+  }
 }
 
 void fill_event_args(const rta_pipeline* pipe, rta::EventArgs& ea);
@@ -885,7 +899,7 @@ rta_status rta_decode_packets(rta_pipeline* pipe, const uint8_t* bytes, int64_t 
   da.pool_elems = pool_elems;
   da.rec = rec;
   da.status = pipe->d_status;
-  RTA_HIP(rta::launch_decode(da, (hipStream_t)stream));
+  RTA_HIP(rta::launch_decode(da, pipe->n_cu, (hipStream_t)stream));
   return RTA_OK;
 }
 

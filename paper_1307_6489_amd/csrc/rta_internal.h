@@ -41,12 +41,23 @@ struct DevCam {
   // Packet CRC constants of this type (multiplications modulo the CRC
   // polynomial): [0, 256) i*K and [256, 512) i*x^8*K with K = x^(16N), the
   // per-lane finishing factors x^(8 a_l) at [512, 768), then x^(8*body) and
-  // 0xFFFF * x^(8*(32+body)) at 768 and 769 (body = 2GTN bytes).
+  // 0xFFFF * x^(8*(32+body)) at 768 and 769 (body = 2GTN bytes).  Then, per
+  // form of kDecodeForms, K^(rows after a slot's last one) per slot and the
+  // two tables of the first kind for K^(step from a slot's block to its next).
   const uint16_t* crc_tab;
 };
 
-constexpr int kCrcTabLen = 770;
-constexpr int kDecodeNT = 256;  // lanes per packet; one 16-byte column piece each (rows <= 4096 bytes)
+// Packet decode forms of more than one slot of lanes per packet: slot s takes
+// the blocks of `rows` consecutive sample rows s, s + slots, ...
+struct DecodeForm {
+  int slots, rows;
+};
+constexpr DecodeForm kDecodeForms[2] = {{2, 4}, {4, 2}};
+constexpr int kDecodeMaxSlots = 4;
+constexpr int crc_after(int form) { return 770 + form * (kDecodeMaxSlots + 512); }
+constexpr int crc_jump(int form) { return crc_after(form) + kDecodeMaxSlots; }
+constexpr int kCrcTabLen = crc_after(2);
+constexpr int kDecodeNT = 256;  // lanes per slot; one 16-byte column piece each (rows <= 4096 bytes)
 constexpr int kDecodePad = RTA_PACKET_PAD;  // readable bytes required after a packet stream
 
 // Network parameters, packed (matches RTA_MLP_N_PARAMS): W1 [10][64], b1,
@@ -166,7 +177,7 @@ hipError_t launch_clean(const DevCam& c, const rta_clean_params* levels, const i
 // Charges from q (p.e.) or, when q is NULL, from D (Q8) and gain.
 hipError_t launch_hillas(const DevCam& c, const float* q, const int32_t* D, const float* t, const uint8_t* mask,
                          const uint8_t* gain, int64_t n_evt, rta_hillas_rec* out, hipStream_t st);
-hipError_t launch_decode(const DecodeArgs& a, hipStream_t st);
+hipError_t launch_decode(const DecodeArgs& a, int n_cu, hipStream_t st);
 // Health accumulation: at most kHealthParts workgroups, each leaving its
 // per-pixel sums in a partial block [3][G][Npad] of the camera's scratch.
 constexpr int kHealthParts = 256;
