@@ -2130,6 +2130,27 @@ constexpr int min_waves() {
 // Kernels
 // ---------------------------------------------------------------------------
 
+// Stores a lane's first n of K consecutive values, in one piece if all are
+// there (an event's outputs begin at any multiple of the value's size).
+// Two pixels' seven outputs in seven stores instead of fourteen: 1000 events of
+// 1855 x 30 samples 35.4 to 33.1 us, of which 31 are the bytes; four pixels per
+// lane 34.3 (twice the registers, half the wavefronts).
+template <int K, typename V>
+__device__ __forceinline__ void store_run(V* dst, const V (&v)[K], int n) {
+  typedef V vec __attribute__((ext_vector_type(K)));
+  typedef vec loose __attribute__((aligned(sizeof(V))));
+  if (n >= K) {
+    vec x;
+#pragma unroll
+    for (int p = 0; p < K; ++p) x[p] = v[p];
+    *reinterpret_cast<loose*>(dst) = x;
+  } else {
+#pragma unroll
+    for (int p = 0; p < K; ++p)
+      if (p < n) dst[p] = v[p];
+  }
+}
+
 // Unfused calibration: one workgroup per camera event, per-pixel results to HBM.
 template <int EX, int PPL, int W, int NT>
 __global__ __launch_bounds__(NT) void k_calibrate(DevCam c, const uint16_t* __restrict__ traces, int32_t* S,
@@ -2154,24 +2175,33 @@ __global__ __launch_bounds__(NT) void k_calibrate(DevCam c, const uint16_t* __re
       const int pix0 = (ps * NT + (int)threadIdx.x) * PPL;
       KeepState<PPL> st;
       const uint32_t sw = keep_group<PPL, 2 * W>(c, r, pix0, np, T, c.n_gain == 2, st);
+if (pix0 >= N) continue;
+      int32_t sum[PPL], d[PPL];
+      uint8_t s[PPL], pk[PPL], g[PPL];
+      float qv[PPL], tv[PPL];
 #pragma unroll
       for (int p = 0; p < PPL; ++p) {
-        const int i = pix0 + p;
-        if (i >= N) break;
-        const int g = (sw >> p) & 1;
-        const int s = 255 - (int)(st.key[p] & 255u);
-        const int32_t P = c.P256[g * np + i];
-        const int32_t d = key_to_d<W>(st.key[p], P);
-        int pk;
-        const int32_t nt = kept_nt(st.sv0[p], st.sv1[p], P, s, &pk);
-        if (S) S[ob + i] = (int32_t)(st.key[p] >> 8);
-        if (D) D[ob + i] = d;
-        if (sstar) sstar[ob + i] = (uint8_t)s;
-        if (peak) peak[ob + i] = (uint8_t)pk;
-        if (gain) gain[ob + i] = (uint8_t)g;
-        if (q) q[ob + i] = (float)d / (256.0f * c.a[g * np + i]);
-        if (t) t[ob + i] = (float)peak_time<W>(s, nt, d);
+        g[p] = (uint8_t)((sw >> p) & 1);
+        const int o = g[p] * np + pix0 + p;  // padding pixels have table entries
+        s[p] = (uint8_t)(255 - (int)(st.key[p] & 255u));
+        const int32_t P = c.P256[o];
+        sum[p] = (int32_t)(st.key[p] >> 8);
+        d[p] = key_to_d<W>(st.key[p], P);
+        int peak_at;
+        const int32_t nt = kept_nt(st.sv0[p], st.sv1[p], P, s[p], &peak_at);
+        pk[p] = (uint8_t)peak_at;
+        qv[p] = (float)d[p] / (256.0f * c.a[o]);
+        tv[p] = (float)peak_time<W>(s[p], nt, d[p]);
       }
+      const size_t at = ob + pix0;
+      const int n = N - pix0;
+      if (S) store_run(S + at, sum, n);
+      if (D) store_run(D + at, d, n);
+      if (sstar) store_run(sstar + at, s, n);
+      if (peak) store_run(peak + at, pk, n);
+      if (gain) store_run(gain + at, g, n);
+      if (q) store_run(q + at, qv, n);
+      if (t) store_run(t + at, tv, n);
     }
     return;
   }
@@ -2206,10 +2236,22 @@ __global__ __launch_bounds__(NT) void k_clean(DevCam c, const int32_t* __restric
   const int64_t e = blockIdx.x;
   const int N = c.n_pix;
   const size_t ob = (size_t)e * N;
-  for (int i = threadIdx.x; i < N; i += NT) {
-    const int g = gain ? (int)gain[ob + i] : 0;
-    sm.flag[i] = (uint8_t)(have_levels ? pixel_flag_at(c, g, i, D[ob + i], t_pic, t_bnd)
-                                       : pixel_flag(c, g, i, D[ob + i]));
+  // pixels per thread, their loads all in flight (1000 events of 1855 pixels:
+  // 9.4 us, 10.1 with one pixel after the other)
+  constexpr int K = kMaxPix / NT;
+  int32_t d[K];
+  int g[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = min(k * NT + (int)threadIdx.x, N - 1);
+    g[k] = gain ? (int)gain[ob + i] : 0;
+    d[k] = D[ob + i];
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = k * NT + (int)threadIdx.x, at = min(i, N - 1);
+    const uint32_t fl = have_levels ? pixel_flag_at(c, g[k], at, d[k], t_pic, t_bnd) : pixel_flag(c, g[k], at, d[k]);
+    if (i < N) sm.flag[i] = (uint8_t)fl;
   }
   __syncthreads();
   mask_phase<NT>(c, sm);
