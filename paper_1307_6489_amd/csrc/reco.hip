@@ -1163,7 +1163,7 @@ __device__ __forceinline__ uint32_t pixel_flag_at(const DevCam& c, int g, int i,
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup-shared state of one camera event: 16.4 KB, so that LDS lets nine
+// Workgroup-shared state of one camera event: 16.5 KB, so that LDS lets nine
 // 256-thread workgroups share a compute unit (it was 32.3 KB, five, while
 // every mask pixel had its packed charge and time here; the fixed window,
 // bound by how many telescopes are in flight, runs by it).
