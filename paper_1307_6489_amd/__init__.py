@@ -665,7 +665,7 @@ class Sam:
         noff = torch.empty(shape, dtype=torch.int32, device=dev) if maps else None
         # the count's row and the alerts in one buffer, read back by one copy:
         # each copy waits for the device, three of them took 30 us more
-        buf = torch.empty((max(int(max_alerts), 0) + 1, 4), dtype=torch.float64, device=dev)
+        buf = torch.empty((max(max_alerts, 0) + 1, 4), dtype=torch.float64, device=dev)
         _check(lib().rta_sam_search(self.handle, int(end_bin), _ptr(sig), _ptr(non), _ptr(noff), _ptr(buf[1:]),
                                     int(max_alerts), _ptr(buf), _stream(stream)))
         host = buf.cpu().numpy()
