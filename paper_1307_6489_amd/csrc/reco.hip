@@ -41,6 +41,7 @@
 
 #include "descriptors.h"
 #include "mlp_device.h"
+#include "pixel_runs.h"
 #include "rta_internal.h"
 
 namespace rta {
@@ -1330,10 +1331,11 @@ __device__ __forceinline__ void store_flags(uint8_t* dst, uint64_t fl) {
 template <int EX, int PPL, int W, int CH, int NT, bool BOUND>
 __device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __restrict__ ev, TelSmem& sm,
                                              uint16_t* xrow) {
+  static_assert(kRunWave == kWave && kMaxPix % run_length(kMaxPix, NT, PPL) == 0, "whole runs fill the list");
   const int N = c.n_pix, np = c.n_pix_pad;
   const int wave = threadIdx.x / kWave;
   const __amdgpu_buffer_rsrc_t r = event_rsrc(ev, c.event_elems);
-  uint16_t* cand = sm.list + wave * (kMaxPix / (NT / kWave));
+  uint16_t* cand = sm.list + run_begin(kMaxPix, NT, PPL, wave);
   int ncand = 0, nlow = 0;
   if (threadIdx.x < kMaxWords) sm.mbits[threadIdx.x] = 0ull;
   auto take = [&](int pix0, const uint32_t (&key)[PPL], uint32_t sw) {
@@ -1800,11 +1802,11 @@ __device__ __forceinline__ rta_hillas_rec large_image(const DevCam& c, TelSmem& 
 // mask words.  In an image of at most 64 mask pixels (95 % of the throughput
 // mix) every pixel's lane then writes its slot and edges, and wavefront 0
 // ends alone; the other wavefronts return an unused record.
-template <int NT, int W>
+template <int PPL, int NT, int W>
 __device__ __forceinline__ rta_hillas_rec fused_image(const DevCam& c, TelSmem& sm, int ncand,
                                                       const uint16_t* __restrict__ ev) {
   const int np = c.n_pix_pad, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const uint16_t* cand = sm.list + wave * (kMaxPix / (NT / kWave));
+  const uint16_t* cand = sm.list + run_begin(kMaxPix, NT, PPL, wave);
   uint32_t* m32 = reinterpret_cast<uint32_t*>(sm.mbits);
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   const bool has = lane < ncand;
@@ -1931,14 +1933,14 @@ __device__ __forceinline__ rta_hillas_rec given_image(const DevCam& c, TelSmem& 
 // cache lines a second time (1.35 times the trace in all).  Returns false if more than kNbrAsk pixels are asked or more than kNbrStage traces
 // needed: every pixel is then scanned, from the start.  none: set when no
 // pixel is asked.
-template <int NT, int W>
+template <int PPL, int NT, int W>
 __device__ __forceinline__ bool nbr_windows(const DevCam& c, NbrSmem& nm, int ncand, const uint16_t* __restrict__ ev,
                                             bool* none) {
   TelSmem& sm = nm.tel;
   constexpr int NW = NT / kWave;
   const int np = c.n_pix_pad, T = c.n_samp, nw = (c.n_pix + 63) >> 6;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const uint16_t* cand = sm.list + wave * (kMaxPix / NW);
+  const uint16_t* cand = sm.list + run_begin(kMaxPix, NT, PPL, wave);
   uint32_t* m32 = reinterpret_cast<uint32_t*>(sm.mbits);
   auto each_neighbour = [](const int4& nv, auto&& fn) {
     const int32_t nb2[3] = {nv.x, nv.y, nv.z};
@@ -2097,15 +2099,15 @@ __device__ __forceinline__ rta_hillas_rec process_telescope(const DevCam& c, con
     if (!c.nbr_scan) {
       const int ncand = extract_phase<EX, PPL, W, CH, NT, true>(c, ev, sm, xrow);
       bool none;
-      if (nbr_windows<NT, W>(c, nm, ncand, ev, &none)) {
+      if (nbr_windows<PPL, NT, W>(c, nm, ncand, ev, &none)) {
         if (none) return empty_image(total_count<NT>(sm));
-        return fused_image<NT, W>(c, sm, ncand, ev);
+        return fused_image<PPL, NT, W>(c, sm, ncand, ev);
       }
       __syncthreads();  // the wavefronts' runs and the mask words have been read
     }
   }
   const int ncand = extract_phase<EX, PPL, W, CH, NT, false>(c, ev, sm, xrow);
-  return fused_image<NT, W>(c, sm, ncand, ev);
+  return fused_image<PPL, NT, W>(c, sm, ncand, ev);
 }
 
 __device__ __forceinline__ void bad_record(rta_hillas_rec* out) {
