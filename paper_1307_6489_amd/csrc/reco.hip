@@ -2122,10 +2122,13 @@ __device__ __forceinline__ void bad_record(rta_hillas_rec* out) {
 // Waves per SIMD the register allocation must leave room for: the neighbour
 // peak's 256-thread workgroups fit four to a compute unit by their LDS (37
 // KB), if the registers allow it; its full scan, bound by latency, loses 8 %
-// with three.  Elsewhere the compiler's own choice stands.
+// with three.  The sliding window keeps two: with 8 pixels per lane, chunks
+// of 16 and 4 wavefronts the compiler's own choice is 260 registers, one wave
+// (8000 events of the 1:3:6 mix 600 us, 457 with two).  Elsewhere that choice
+// stands.
 template <int EX, int NT>
 constexpr int min_waves() {
-  return EX == kExNeighbour && NT == 256 ? 4 : 1;
+  return EX == kExNeighbour && NT == 256 ? 4 : EX == kExSliding ? 2 : 1;
 }
 
 // ---------------------------------------------------------------------------
