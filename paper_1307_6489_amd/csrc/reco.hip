@@ -1051,7 +1051,9 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
 }
 
 // Upper bounds for the neighbour peak: the sliding window's key on the high
-// gain of every pixel group, and its low-gain bits.
+// gain of every pixel group, and its low-gain bits.  With 8 pixels per lane in
+// chunks of 8: chunks of 16 need 190 registers, or 316 bytes of scratch (8000
+// events of the 1:3:6 mix 1172 us, 596 with chunks of 8).
 template <int PPL, int W, int CH, int NT, class Fn>
 __device__ __forceinline__ void bound_event(const DevCam& c, __amdgpu_buffer_rsrc_t r, Fn&& fn) {
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
@@ -1061,7 +1063,7 @@ __device__ __forceinline__ void bound_event(const DevCam& c, __amdgpu_buffer_rsr
     uint32_t key[PPL], rmax[PPL / 2];
 #pragma unroll
     for (int h = 0; h < PPL / 2; ++h) rmax[h] = 0;
-    window_argmax<PPL, W, CH, true>(r, (uint32_t)pix0 * 2u, 0u, (uint32_t)np * 2u, T, key, rmax);
+    window_argmax<PPL, W, PPL == 8 ? 8 : CH, true>(r, (uint32_t)pix0 * 2u, 0u, (uint32_t)np * 2u, T, key, rmax);
     uint32_t sw = 0;
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
