@@ -19,7 +19,7 @@ struct rta_camera {
   rta::DevCam dev;
   void* dmem = nullptr;
   rta_camera_info info{};
-  int device = 0;
+  int device = 0, n_cu = 0;
   uint64_t* health_acc = nullptr;   // [2][G][Npad] health rms (bits) and flags, inside dmem
   uint64_t* health_part = nullptr;  // [kHealthParts / G][3][G][Npad] per-workgroup partial sums, inside dmem
   double max_a = 0.0;                // largest adc_per_pe of the camera (threshold range checks)
@@ -444,7 +444,9 @@ rta_status rta_camera_create(const rta_camera_desc* d, rta_camera** out) {
   std::memcpy(host.data() + oLP, lpos.data(), lpos.size() * 2);
   rta_camera* cam = new (std::nothrow) rta_camera();
   if (!cam) return fail(RTA_E_NOMEM, "host allocation failed");
-  if (hipGetDevice(&cam->device) != hipSuccess || hipMalloc(&cam->dmem, total) != hipSuccess) {
+  if (hipGetDevice(&cam->device) != hipSuccess ||
+      hipDeviceGetAttribute(&cam->n_cu, hipDeviceAttributeMultiprocessorCount, cam->device) != hipSuccess ||
+      hipMalloc(&cam->dmem, total) != hipSuccess) {
     delete cam;
     return fail(RTA_E_NOMEM, "device allocation for camera tables failed");
   }
@@ -516,7 +518,7 @@ rta_status rta_calibrate_ex(const rta_camera* cam, int32_t extractor, const uint
   if (n_evt > 0x7fffffffLL) return fail(RTA_E_SHAPE, "too many events for one launch");
   if (n_evt == 0) return RTA_OK;
   if (!traces || !aligned16(traces)) return fail(RTA_E_INVALID_ARG, "traces must be non-null and 16-byte aligned");
-  RTA_HIP(rta::launch_calibrate(cam->dev, extractor, traces, n_evt, S, D, sstar, peak, gain, q, t,
+  RTA_HIP(rta::launch_calibrate(cam->dev, extractor, traces, n_evt, cam->n_cu, S, D, sstar, peak, gain, q, t,
                                 (hipStream_t)stream));
   return RTA_OK;
 }

@@ -167,8 +167,8 @@ hipError_t launch_mlp_adam(const MlpDev& w, bool update, float lr, float b1, flo
                            hipStream_t st);
 
 // Kernel launchers (reco.hip).  Each returns the launch status.
-hipError_t launch_calibrate(const DevCam& c, int extractor, const uint16_t* traces, int64_t n_evt, int32_t* S,
-                            int32_t* D, uint8_t* sstar, uint8_t* peak, uint8_t* gain, float* q, float* t,
+hipError_t launch_calibrate(const DevCam& c, int extractor, const uint16_t* traces, int64_t n_evt, int n_cu,
+                            int32_t* S, int32_t* D, uint8_t* sstar, uint8_t* peak, uint8_t* gain, float* q, float* t,
                             hipStream_t st);
 // levels: NULL for the camera's threshold tables, else the two levels whose
 // thresholds the kernel forms per pixel as the camera creation does.
