@@ -2610,6 +2610,43 @@ __global__ __launch_bounds__(256) void k_features(const rta_hillas_rec* __restri
   for (int f = 0; f < mlpdev::kIn; ++f) x[i * mlpdev::kIn + f] = mlpdev::record_feature(r, f);
 }
 
+struct BoxTables {
+  float w_mean[RTA_BOXCUT_MAX_BINS], w_std[RTA_BOXCUT_MAX_BINS], l_mean[RTA_BOXCUT_MAX_BINS],
+      l_std[RTA_BOXCUT_MAX_BINS];
+};
+
+__device__ __forceinline__ void load_tables(const rta_boxcut_desc& bc, BoxTables& tab) {
+  static_assert(RTA_BOXCUT_MAX_BINS <= kWave, "a bin per lane");
+  const int k = threadIdx.x;
+  if (k < RTA_BOXCUT_MAX_BINS) {
+    tab.w_mean[k] = bc.w_mean[k];
+    tab.w_std[k] = bc.w_std[k];
+    tab.l_mean[k] = bc.l_mean[k];
+    tab.l_std[k] = bc.l_std[k];
+  }
+}
+
+__device__ __forceinline__ void store_class(float* dst, const mlpdev::ClassOut& co) {
+  dst[0] = co.score;
+  dst[1] = co.log10e;
+  dst[2] = (float)co.gamma;
+  dst[3] = (float)co.fallback;
+}
+
+// Without a network: a record per thread, as many wavefronts as there are
+// (the persistent tiles of the network, 16 records per wavefront and round on
+// two wavefronts per SIMD, took 70.7 us for 2000000 records; 23.6 so).
+__global__ __launch_bounds__(256) void k_classify_box(rta_boxcut_desc bc, const rta_hillas_rec* __restrict__ rec,
+                                                      int64_t n, float* __restrict__ out) {
+  __shared__ BoxTables tab;
+  load_tables(bc, tab);
+  __syncthreads();
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n)
+    store_class(out + i * 4, mlpdev::classify_decide(rec[i], bc, tab.w_mean, tab.w_std, tab.l_mean, tab.l_std, false,
+                                                     0.f, 0.f));
+}
+
 // Per-record classification, 16 records per wavefront and round.  The network
 // is 18 kFLOP a record against 80 bytes of memory, but with its 18 KB of
 // weights read from L2 for every tile, layer by layer, 200000 records took
@@ -2621,30 +2658,23 @@ __global__ __launch_bounds__(256) void k_features(const rta_hillas_rec* __restri
 // divisions, four dependent layers) with few wavefronts to cover it.  Three
 // wavefronts per SIMD with the biases in LDS (147 registers), 25.5, and one
 // per SIMD, 27.3, were slower: each wavefront loads the weights once.
-__global__ __launch_bounds__(kWave) void k_classify(MlpDev w, int have_mlp, rta_boxcut_desc bc,
+__global__ __launch_bounds__(kWave) void k_classify(MlpDev w, rta_boxcut_desc bc,
                                                     const rta_hillas_rec* __restrict__ rec, int64_t n,
                                                     float* __restrict__ out) {
-  __shared__ float tab[4][RTA_BOXCUT_MAX_BINS];
+  __shared__ BoxTables tab;
   const int lane = threadIdx.x, col = lane & 15, grp = lane >> 4;
-  if (lane < RTA_BOXCUT_MAX_BINS) {
-    tab[0][lane] = bc.w_mean[lane];
-    tab[1][lane] = bc.w_std[lane];
-    tab[2][lane] = bc.l_mean[lane];
-    tab[3][lane] = bc.l_std[lane];
-  }
+  load_tables(bc, tab);
   // a lane has features 4 grp .. 4 grp + 3 of row col: their standardisation
   // and trained range
-  mlpdev::MlpFrag net = {};
-  float mean[4] = {0.f, 0.f, 0.f, 0.f}, stdv[4] = {1.f, 1.f, 1.f, 1.f}, lo[4], hi[4];
-  if (have_mlp) {
-    mlpdev::mlp_load(w, net);
-    mlpdev::load_scale(w, grp, mean, stdv);
+  mlpdev::MlpFrag net;
+  float mean[4], stdv[4], lo[4], hi[4];
+  mlpdev::mlp_load(w, net);
+  mlpdev::load_scale(w, grp, mean, stdv);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int f = min(4 * grp + j, mlpdev::kIn - 1);
-      lo[j] = bc.feat_lo[f];
-      hi[j] = bc.feat_hi[f];
-    }
+  for (int j = 0; j < 4; ++j) {
+    const int f = min(4 * grp + j, mlpdev::kIn - 1);
+    lo[j] = bc.feat_lo[f];
+    hi[j] = bc.feat_hi[f];
   }
   __syncthreads();
   const int64_t step = (int64_t)gridDim.x * 16;
@@ -2653,31 +2683,19 @@ __global__ __launch_bounds__(kWave) void k_classify(MlpDev w, int have_mlp, rta_
   for (; r0 < n; r0 += step) {
     const rta_hillas_rec r = next;
     if (r0 + step < n) next = rec[min(r0 + step + col, n - 1)];
-    float logit = 0.f, me = 0.f;
-    bool in_range = false;
-    if (have_mlp) {
-      float x[4];
-      mlpdev::record_features4(r, grp, x);
-      bool ok = true;
+    float x[4];
+    mlpdev::record_features4(r, grp, x);
+    bool ok = true;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        ok = ok && (4 * grp + j >= mlpdev::kIn || (isfinite(x[j]) && x[j] >= lo[j] && x[j] <= hi[j]));
-      const uint64_t m = __ballot(ok);  // row col is in range when its four lanes' features are
-      in_range = (m >> col & m >> (col + 16) & m >> (col + 32) & m >> (col + 48)) & 1ull;
-      mlpdev::bf16x4 h1[4], h2[4], h3[4];
-      const mlpdev::f32x4 o = mlpdev::mlp_forward(net, mlpdev::record_inputs(x, mean, stdv), h1, h2, h3);
-      logit = o[0];
-      me = o[1];
-    }
-    if (grp == 0 && r0 + col < n) {
-      const mlpdev::ClassOut co =
-          mlpdev::classify_decide(r, bc, tab[0], tab[1], tab[2], tab[3], in_range, logit, me);
-      float* dst = out + (r0 + col) * 4;
-      dst[0] = co.score;
-      dst[1] = co.log10e;
-      dst[2] = (float)co.gamma;
-      dst[3] = (float)co.fallback;
-    }
+    for (int j = 0; j < 4; ++j)
+      ok = ok && (4 * grp + j >= mlpdev::kIn || (isfinite(x[j]) && x[j] >= lo[j] && x[j] <= hi[j]));
+    const uint64_t m = __ballot(ok);  // row col is in range when its four lanes' features are
+    const bool in_range = (m >> col & m >> (col + 16) & m >> (col + 32) & m >> (col + 48)) & 1ull;
+    mlpdev::bf16x4 h1[4], h2[4], h3[4];
+    const mlpdev::f32x4 o = mlpdev::mlp_forward(net, mlpdev::record_inputs(x, mean, stdv), h1, h2, h3);
+    if (grp == 0 && r0 + col < n)
+      store_class(out + (r0 + col) * 4, mlpdev::classify_decide(r, bc, tab.w_mean, tab.w_std, tab.l_mean, tab.l_std,
+                                                                in_range, o[0], o[1]));
   }
 }
 
@@ -2848,11 +2866,14 @@ hipError_t launch_features(const rta_hillas_rec* rec, int64_t n, float* x, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_classify(const MlpDev& w, bool have_mlp, const rta_boxcut_desc& bc, const rta_hillas_rec* rec,
-                           int64_t n, float* out, hipStream_t st) {
-  const int64_t tiles = (n + 15) / 16, most = 8 * 256;  // two wavefronts per SIMD of 256 compute units
-  hipLaunchKernelGGL(k_classify, dim3((unsigned)(tiles < most ? tiles : most)), dim3(kWave), 0, st, w,
-                     have_mlp ? 1 : 0, bc, rec, n, out);
+hipError_t launch_classify(const MlpDev* w, int n_cu, const rta_boxcut_desc& bc, const rta_hillas_rec* rec, int64_t n,
+                           float* out, hipStream_t st) {
+  const int64_t tiles = (n + 15) / 16, most = 8 * (int64_t)n_cu;  // two wavefronts per SIMD
+  if (w)
+    hipLaunchKernelGGL(k_classify, dim3((unsigned)(tiles < most ? tiles : most)), dim3(kWave), 0, st, *w, bc, rec, n,
+                       out);
+  else
+    hipLaunchKernelGGL(k_classify_box, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bc, rec, n, out);
   return hipGetLastError();
 }
 

@@ -57,7 +57,7 @@ struct rta_graph {
 struct rta_mlp {
   rta::MlpDev dev{};
   void* dmem = nullptr;
-  int max_batch = 0, bpad_max = 0;
+  int max_batch = 0, bpad_max = 0, n_cu = 0;
   int64_t last_B = 0;  // batch of the last loss_grad / train_step pass (0: none yet)
   float lr = 1e-3f, beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
   int64_t step = 0;
@@ -1115,8 +1115,7 @@ rta_status rta_classify(rta_mlp* m, const rta_boxcut_desc* bc, const rta_hillas_
   if (n == 0) return RTA_OK;
   if (!rec || !out) return fail(RTA_E_INVALID_ARG, "null pointer");
   if ((n + 63) / 64 > 0x7fffffffLL) return fail(RTA_E_SHAPE, "too many records for one launch");
-  rta::MlpDev none{};
-  RTA_HIP(rta::launch_classify(m ? m->dev : none, m != nullptr, *bc, rec, n, out, (hipStream_t)stream));
+  RTA_HIP(rta::launch_classify(m ? &m->dev : nullptr, m ? m->n_cu : 0, *bc, rec, n, out, (hipStream_t)stream));
   return RTA_OK;
 }
 
@@ -1160,7 +1159,10 @@ rta_status rta_mlp_create(const rta_mlp_desc* d, rta_mlp** out) {
   const int n = sizeof(sizes) / sizeof(sizes[0]);
   size_t off[32], total = 0;
   for (int i = 0; i < n; ++i) { off[i] = total; total += round256(sizes[i]); }
-  if (hipMalloc(&m->dmem, total) != hipSuccess) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&m->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipMalloc(&m->dmem, total) != hipSuccess) {
     delete m;
     return fail(RTA_E_NOMEM, "device allocation for the network failed");
   }

@@ -197,8 +197,9 @@ hipError_t launch_fused(const FusedArgs& a, const rta_schedule& s, int n_cu, hip
 hipError_t launch_event(const EventArgs& a, int n_cu, hipStream_t st);
 hipError_t launch_stamp(uint64_t* slot, hipStream_t st);
 hipError_t launch_features(const rta_hillas_rec* rec, int64_t n, float* x, hipStream_t st);
-hipError_t launch_classify(const MlpDev& w, bool have_mlp, const rta_boxcut_desc& bc, const rta_hillas_rec* rec,
-                           int64_t n, float* out, hipStream_t st);
+// w: NULL without a network.
+hipError_t launch_classify(const MlpDev* w, int n_cu, const rta_boxcut_desc& bc, const rta_hillas_rec* rec, int64_t n,
+                           float* out, hipStream_t st);
 
 bool window_supported(int w);
 bool extractor_supported(int ex);
