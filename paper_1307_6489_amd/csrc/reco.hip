@@ -817,31 +817,36 @@ __device__ __forceinline__ int global_start(const uint32_t* rows, int T, int32_t
 // PPL-pixel groups.  The raw high-gain maximum (gain decision on the whole
 // trace, as for the sliding window) is kept where the slices are staged.
 //
-// nbr_scan makes the pass over the slices.  With EXACT, the neighbour and
-// window sums are formed in 32 bits.  Without, everything stays in saturating
-// packed 16-bit halves, two slices to a register: the neighbour sums, the
-// window sums C(k) = p(k) + p(k - 2) with p(k) = y(k) + y(k - 1) (one funnel
-// shift per two slices gives the pairs), and a key is one byte permute of
-// the halfword with the slice's index byte: 24 vector instructions per pixel
-// and four slices where the 32-bit form takes about 50 (the mix 1123 -> 1042
-// us: the scan waits more for LDS and barriers than for them).  A best sum of 65535
-// says that some sum may not have fitted, and the event is scanned again in
-// 32 bits (returned true; an image has to put some 8500 p.e. into six
-// pixels); a camera whose pedestals alone bring the sums near that
-// (DevCam::nbr_exact) is scanned in 32 bits at once.
-template <int W, int NT, bool EXACT>
-__device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t r, uint64_t* xs, uint32_t* keys,
-                                         uint8_t* low, int32_t* again) {
+// nbr_scan makes the pass over the slices.  Sums stay in saturating packed
+// 16-bit halves, two slices to a register, while they fit: the neighbour sums,
+// the window sums C(k) = p(k) + p(k - 2) with p(k) = y(k) + y(k - 1) (one
+// funnel shift per two slices gives the pairs), and a key is one byte permute
+// of the halfword with the slice's index byte: 24 vector instructions per
+// pixel and four slices where the 32-bit form takes about 50 (the mix 1123 ->
+// 1042 us: the scan waits more for LDS and barriers than for them).  Every
+// neighbour sum of four slices is part of a window sum that is ranked with
+// them, so a best sum below 65535 says that all of them fitted.  Otherwise (an
+// image has to put some 8500 p.e. into six pixels, or the pedestals do) the
+// wavefront forms these four slices again in 32 bits, from the state before
+// them, and stays there until the trace ends.  (An event that was repeated
+// from the start in 32 bits took 129 us by itself, 65 so, 61 where all sums
+// fit; 200 bright events 160 us and 93; 2048 x 128.)
+template <int W, int NT>
+__device__ __forceinline__ void nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t r, uint64_t* xs, uint32_t* keys,
+                                         uint8_t* low) {
   static_assert(kNbrRows == 4 && W == 4, "four slices per staged pixel word pair, windows of four");
   constexpr int MAXK = (kMaxPix + NT - 1) / NT;  // pixels per lane: t, t + NT, ...
+  static_assert(MAXK % 2 == 0, "positions go in pairs");
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
   // position p = 8 g + m lives in word 8 g + (m ^ (g & 7)): consecutive
   // lanes reading consecutive positions touch distinct banks
   auto slot = [](uint32_t j) { return (j & ~7u) | ((j ^ (j >> 3)) & 7u); };
   uint32_t nb[MAXK][3];  // six neighbour words per position: LDS byte offsets, 16 bits each (word Npad if missing)
   uint32_t best[MAXK];
-  us2 yq[EXACT ? 1 : MAXK], pq[EXACT ? 1 : MAXK];  // y(k0-2), y(k0-1) and p(k0-2), p(k0-1)
-  uint32_t ring[EXACT ? MAXK : 1][W - 1];          // y(k0-1), y(k0-2), y(k0-3)
+  // in halves, (y(k0-2), y(k0-1)) and (p(k0-2), p(k0-1)); in 32 bits, y(k0-1),
+  // y(k0-2) and y(k0-3), 19 bits each (six samples)
+  uint32_t st[MAXK][2];
+  bool wide = false;  // in 32 bits, uniform over the wavefront
 #pragma unroll
   for (int k = 0; k < MAXK; ++k) {
     const int p = (int)threadIdx.x + k * NT;
@@ -856,18 +861,10 @@ __device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t
         nb[k][h] = (lo << 3) | (hi << 19);  // (Npad + 1) * 8 bytes < 2^16
       }
     }
-    if constexpr (EXACT) {
-#pragma unroll
-      for (int u = 0; u < W - 1; ++u) ring[k][u] = 0;
-    } else {
-      yq[k] = pq[k] = us2{0, 0};
-    }
+    st[k][0] = st[k][1] = 0;
     best[k] = 0;
   }
-  if (threadIdx.x == 0) {
-    xs[np] = 0ull;
-    *again = 0;
-  }
+  if (threadIdx.x == 0) xs[np] = 0ull;
   // thread q stages 16-byte pixel group q (np / 8 <= kMaxPix / 8 <= NT
   // groups), the next four slices loaded while the current ones are used
   static_assert(kMaxPix / 8 <= NT, "one staged pixel group per thread");
@@ -920,79 +917,99 @@ __device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t
     const uint32_t idx = (key0 & 255u) | (((key0 - 1u) & 255u) << 8) | (((key0 - 2u) & 255u) << 16) |
                          (((key0 - 3u) & 255u) << 24);
     // positions past the camera read the zero word; their keys are not used
-    auto take = [&](int k, bool whole) {
-      uint64_t v[6];
+    auto load = [&](int k, uint64_t (&v)[6]) {
 #pragma unroll
       for (int m = 0; m < 6; ++m) {
         const uint32_t off = (nb[k][m >> 1] >> ((m & 1) * 16)) & 0xffffu;
         v[m] = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(xs) + off);
       }
-      if constexpr (EXACT) {
-        uint32_t y[kNbrRows] = {0, 0, 0, 0};
+    };
+    // in halves: the state after these slices in s, the best key returned
+    auto halves = [&](int k, uint32_t (&s)[2], bool whole) {
+      uint64_t v[6];
+      load(k, v);
+      us2 s01 = __builtin_bit_cast(us2, (uint32_t)v[0]), s23 = __builtin_bit_cast(us2, (uint32_t)(v[0] >> 32));
 #pragma unroll
-        for (int m = 0; m < 6; ++m) {
-          const uint32_t v01 = (uint32_t)v[m], v23 = (uint32_t)(v[m] >> 32);
-          y[0] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v01), row_lo, y[0], false);
-          y[1] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v01), row_hi, y[1], false);
-          y[2] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_lo, y[2], false);
-          y[3] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_hi, y[3], false);
-        }
-#pragma unroll
-        for (int u = 0; u < kNbrRows; ++u) {
-          const int t = k0 + u;
-          if (t >= T) break;
-          uint32_t C = y[u];
-#pragma unroll
-          for (int z = 0; z < W - 1; ++z) C += ring[k][z];
-          if (t >= W - 1) best[k] = max(best[k], (C << 8) | (uint32_t)(255 - (t - (W - 1))));
-#pragma unroll
-          for (int z = W - 2; z > 0; --z) ring[k][z] = ring[k][z - 1];
-          ring[k][0] = y[u];
-        }
+      for (int m = 1; m < 6; ++m) {
+        s01 = __builtin_elementwise_add_sat(s01, __builtin_bit_cast(us2, (uint32_t)v[m]));
+        s23 = __builtin_elementwise_add_sat(s23, __builtin_bit_cast(us2, (uint32_t)(v[m] >> 32)));
+      }
+      // (y(k0-1), y(k0)) and (y(k0+1), y(k0+2))
+      const us2 m10 =
+          __builtin_bit_cast(us2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, s01), st[k][0], 16));
+      const us2 s12 = __builtin_bit_cast(us2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, s23),
+                                                                        __builtin_bit_cast(uint32_t, s01), 16));
+      const us2 p01 = __builtin_elementwise_add_sat(s01, m10), p23 = __builtin_elementwise_add_sat(s23, s12);
+      const uint32_t C01 = __builtin_bit_cast(
+          uint32_t, __builtin_elementwise_add_sat(p01, __builtin_bit_cast(us2, st[k][1])));
+      const uint32_t C23 = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(p23, p01));
+      s[0] = __builtin_bit_cast(uint32_t, s23);
+      s[1] = __builtin_bit_cast(uint32_t, p23);
+      // (C << 8) | index byte: bytes 4..7 of the permute are C's, 0..3 the indices'
+      const uint32_t kk[kNbrRows] = {
+          __builtin_amdgcn_perm(C01, idx, 0x0c050400u), __builtin_amdgcn_perm(C01, idx, 0x0c070601u),
+          __builtin_amdgcn_perm(C23, idx, 0x0c050402u), __builtin_amdgcn_perm(C23, idx, 0x0c070603u)};
+      if (whole) {
+        best[k] = max(max(best[k], kk[0]), kk[1]);
+        best[k] = max(max(best[k], kk[2]), kk[3]);
       } else {
-        us2 s01 = __builtin_bit_cast(us2, (uint32_t)v[0]), s23 = __builtin_bit_cast(us2, (uint32_t)(v[0] >> 32));
 #pragma unroll
-        for (int m = 1; m < 6; ++m) {
-          s01 = __builtin_elementwise_add_sat(s01, __builtin_bit_cast(us2, (uint32_t)v[m]));
-          s23 = __builtin_elementwise_add_sat(s23, __builtin_bit_cast(us2, (uint32_t)(v[m] >> 32)));
-        }
-        // (y(k0-1), y(k0)) and (y(k0+1), y(k0+2))
-        const us2 m10 = __builtin_bit_cast(us2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, s01),
-                                                                          __builtin_bit_cast(uint32_t, yq[k]), 16));
-        const us2 s12 = __builtin_bit_cast(us2, __builtin_amdgcn_alignbit(__builtin_bit_cast(uint32_t, s23),
-                                                                          __builtin_bit_cast(uint32_t, s01), 16));
-        const us2 p01 = __builtin_elementwise_add_sat(s01, m10), p23 = __builtin_elementwise_add_sat(s23, s12);
-        const uint32_t C01 = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(p01, pq[k]));
-        const uint32_t C23 = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(p23, p01));
-        yq[k] = s23;
-        pq[k] = p23;
-        // (C << 8) | index byte: bytes 4..7 of the permute are C's, 0..3 the indices'
-        const uint32_t kk[kNbrRows] = {__builtin_amdgcn_perm(C01, idx, 0x0c050400u),
-                                       __builtin_amdgcn_perm(C01, idx, 0x0c070601u),
-                                       __builtin_amdgcn_perm(C23, idx, 0x0c050402u),
-                                       __builtin_amdgcn_perm(C23, idx, 0x0c070603u)};
-        if (whole) {
-          best[k] = max(max(best[k], kk[0]), kk[1]);
-          best[k] = max(max(best[k], kk[2]), kk[3]);
-        } else {
-#pragma unroll
-          for (int u = 0; u < kNbrRows; ++u)
-            if (k0 + u >= W - 1 && k0 + u < T) best[k] = max(best[k], kk[u]);
-        }
+        for (int u = 0; u < kNbrRows; ++u)
+          if (k0 + u >= W - 1 && k0 + u < T) best[k] = max(best[k], kk[u]);
       }
     };
-    // two positions at a time without a branch between them, so that the
-    // second's reads are in flight during the first's sums
+    auto exact = [&](int k) {
+      uint64_t v[6];
+      load(k, v);
+      uint32_t y[W - 1 + kNbrRows] = {st[k][1] >> 6, st[k][0] >> 19 | (st[k][1] & 63u) << 13, st[k][0] & 0x7ffffu};
 #pragma unroll
-    for (int k = 0; k < MAXK; k += 2) {
-      if (k * NT >= N) continue;
-      if (!EXACT && full) {
-        take(k, true);
-        if (k + 1 < MAXK) take(k + 1, true);
-      } else {
-        take(k, false);
-        if (k + 1 < MAXK) take(k + 1, false);
+      for (int m = 0; m < 6; ++m) {
+        const uint32_t v01 = (uint32_t)v[m], v23 = (uint32_t)(v[m] >> 32);
+        y[3] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v01), row_lo, y[3], false);
+        y[4] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v01), row_hi, y[4], false);
+        y[5] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_lo, y[5], false);
+        y[6] = __builtin_amdgcn_udot2(__builtin_bit_cast(us2, v23), row_hi, y[6], false);
       }
+#pragma unroll
+      for (int u = 0; u < kNbrRows; ++u)
+        if (k0 + u >= W - 1 && k0 + u < T)
+          best[k] = max(best[k], ((y[u] + y[u + 1] + y[u + 2] + y[u + 3]) << 8) | (uint32_t)(255 - (k0 + u - (W - 1))));
+      st[k][0] = y[6] | y[5] << 19;
+      st[k][1] = y[5] >> 13 | y[4] << 6;
+    };
+    if (!wide) {
+      // two positions at a time without a branch between them, so that the
+      // second's reads are in flight during the first's sums
+      uint32_t s[MAXK][2], top = 0;
+#pragma unroll
+      for (int k = 0; k < MAXK; k += 2) {
+        if (k * NT >= N) continue;
+        if (full) {
+          halves(k, s[k], true);
+          halves(k + 1, s[k + 1], true);
+        } else {
+          halves(k, s[k], false);
+          halves(k + 1, s[k + 1], false);
+        }
+        top = max(max(top, best[k]), best[k + 1]);
+      }
+      wide = __ballot(top >= 0xffff00u) != 0ull;
+#pragma unroll
+      for (int k = 0; k < MAXK; ++k) {
+        if (wide) {
+          const uint32_t y1 = hi16(st[k][0]), y2 = lo16(st[k][0]), y3 = lo16(st[k][1]) - y2;
+          st[k][0] = y1 | y2 << 19;
+          st[k][1] = y2 >> 13 | y3 << 6;
+        } else {
+          st[k][0] = s[k][0];
+          st[k][1] = s[k][1];
+        }
+      }
+    }
+    if (wide) {
+#pragma unroll
+      for (int k = 0; k < MAXK; ++k)
+        if (k * NT < N) exact(k);
     }
   }
   // hand the keys over to the lanes' pixel groups, the low-gain decisions by
@@ -1002,7 +1019,6 @@ __device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t
     const int p = (int)threadIdx.x + k * NT;
     if (p < N) {
       keys[(uint32_t)c.lat[(size_t)p * kNbrCols + 6] & 0xffffu] = best[k];  // the pixel at position p
-      if (!EXACT && best[k] >= 0xffff00u) *again = 1;
     }
   }
   if (stager) {
@@ -1015,7 +1031,6 @@ __device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t
     *reinterpret_cast<uint64_t*>(low + q * 8) = b;
   }
   __syncthreads();
-  return !EXACT && *again != 0;
 }
 
 // The neighbour peak's keys of every pixel group: the scan, then the pixel's
@@ -1024,18 +1039,12 @@ __device__ __forceinline__ bool nbr_scan(const DevCam& c, __amdgpu_buffer_rsrc_t
 template <int PPL, int W, int NT, class Fn>
 __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer_rsrc_t r,
                                                 const uint16_t* __restrict__ ev, uint16_t* xrow, uint32_t* keys,
-                                                uint8_t* low, int32_t* again, Fn&& fn) {
+                                                uint8_t* low, Fn&& fn) {
   constexpr int MAXP = (kMaxPix + NT * PPL - 1) / (NT * PPL);
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
   const int npass = (N + NT * PPL - 1) / (NT * PPL);
   // staged words: slices k0, k0+1 in the low dword, k0+2, k0+3 in the high one
-  uint64_t* xs = reinterpret_cast<uint64_t*>(xrow);
-  bool exact = c.nbr_exact != 0;
-  if (!exact) exact = nbr_scan<W, NT, false>(c, r, xs, keys, low, again);
-  if (exact) {
-    __syncthreads();  // the flag has been read by every thread
-    nbr_scan<W, NT, true>(c, r, xs, keys, low, again);
-  }
+  nbr_scan<W, NT>(c, r, reinterpret_cast<uint64_t*>(xrow), keys, low);
 #pragma unroll
   for (int ps = 0; ps < MAXP; ++ps) {
     if (ps >= npass) continue;
@@ -1107,7 +1116,7 @@ __device__ __forceinline__ void extract_event(const DevCam& c, __amdgpu_buffer_r
       fn(pix0, key, sw);
     }
   } else if constexpr (EX == kExNeighbour) {
-    neighbour_event<PPL, W, NT>(c, r, ev, xrow, rows, low, start, fn);
+    neighbour_event<PPL, W, NT>(c, r, ev, xrow, rows, low, fn);
   } else {
     constexpr int MAXP = (kMaxPix + NT * PPL - 1) / (NT * PPL);
     uint32_t* my_rows = rows + (threadIdx.x / kWave) * 256;

@@ -406,15 +406,6 @@ rta_status rta_camera_create(const rta_camera_desc* d, rta_camera** out) {
     }
     border[i] = cnt < 6 ? 1 : 0;
   }
-  // the neighbour peak's window sums at the pedestals alone: above three
-  // quarters of 16 bits they are formed in 32 at once
-  double nbr_base = 0.0;
-  for (int i = 0; i < N; ++i) {
-    double b = 0.0;
-    for (int k = 0; k < rta::kNbrCols; ++k)
-      if (nb[(size_t)i * rta::kNbrCols + k] >= 0) b += w * (double)d->ped[nb[(size_t)i * rta::kNbrCols + k]];
-    nbr_base = std::max(nbr_base, b);
-  }
   static_assert(rta::kLatCols == rta::kNbrCols, "lattice rows share the neighbour table's width");
   std::vector<int16_t> lat(Np * rta::kNbrCols, -1);
   std::vector<uint16_t> lpos(Np, 0);
@@ -477,7 +468,6 @@ rta_status rta_camera_create(const rta_camera_desc* d, rta_camera** out) {
   c.crc_tab = reinterpret_cast<const uint16_t*>(base + oC);
   c.lat = reinterpret_cast<const int16_t*>(base + oL);
   c.lpos = reinterpret_cast<const uint16_t*>(base + oLP);
-  c.nbr_exact = nbr_base > 49152.0 ? 1 : 0;
   // Levels within the night-sky noise ask for the windows of most pixels.
   // 3000 events of 2048 x 128 at 0.1 p.e. per sample: windows of the asked
   // pixels 340 us at picture / boundary levels of 10 / 5 p.e., 400 at 6 / 3,

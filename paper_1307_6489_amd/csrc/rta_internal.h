@@ -36,7 +36,6 @@ struct DevCam {
   // lpos[j] = the position of pixel j (j itself for padding pixels).
   const int16_t* lat;      // [Npad][8]
   const uint16_t* lpos;    // [Npad]
-  int32_t nbr_exact;       // 1: the neighbour peak's sums do not fit 16 bits at the pedestals
   int32_t nbr_scan;        // 1: the neighbour peak scans every pixel (picture level within the noise)
   // Packet CRC constants of this type (multiplications modulo the CRC
   // polynomial): [0, 256) i*K and [256, 512) i*x^8*K with K = x^(16N), the
