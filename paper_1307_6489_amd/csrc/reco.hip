@@ -41,6 +41,7 @@
 
 #include "descriptors.h"
 #include "mlp_device.h"
+#include "nbr_rule.h"
 #include "pixel_runs.h"
 #include "rta_internal.h"
 
@@ -227,9 +228,11 @@ __device__ __forceinline__ void reduce_chunk(const uint32_t (&cur)[CH][PPL / 2],
   merge_chunk<PPL, W>(k0, loc, key);
 }
 
-template <int PPL, int W, int CH, bool TRACK_MAX>
-__device__ __forceinline__ void window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t sbase, uint32_t stride,
-                                              int T, uint32_t (&key)[PPL], uint32_t (&rmax)[PPL / 2]) {
+// stop(key) is asked after the first chunk, whose windows key then holds, with
+// the second one's loads in flight: true ends the pass, and false is returned.
+template <int PPL, int W, int CH, bool TRACK_MAX, class Stop>
+__device__ __forceinline__ bool window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t sbase, uint32_t stride,
+                                              int T, uint32_t (&key)[PPL], uint32_t (&rmax)[PPL / 2], Stop&& stop) {
   static_assert(CH % W == 0 && CH >= W && CH <= 16, "chunk must be a multiple of the window, at most 16");
   constexpr int ND = PPL / 2;
   uint32_t ws[PPL], loc[PPL];
@@ -244,6 +247,7 @@ __device__ __forceinline__ void window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t
     reduce_chunk<PPL, W, CH, TRACK_MAX, false, true>(A, A, 0, T, ws, loc, key, rmax);
   else
     reduce_chunk<PPL, W, CH, TRACK_MAX, true, true>(A, A, 0, T, ws, loc, key, rmax);
+  if (stop(key)) return false;
   // Chunk c lives in B (odd c) or A (even c); the other buffer holds c - 1.
   for (int c = 1; c < nchunk; c += 2) {
     const int k0 = c * CH;
@@ -266,6 +270,14 @@ __device__ __forceinline__ void window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t
     }
     merge_chunk<PPL, W>(k1, loc, key);
   }
+  return true;
+}
+
+template <int PPL, int W, int CH, bool TRACK_MAX>
+__device__ __forceinline__ void window_argmax(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t sbase, uint32_t stride,
+                                              int T, uint32_t (&key)[PPL], uint32_t (&rmax)[PPL / 2]) {
+  window_argmax<PPL, W, CH, TRACK_MAX>(r, voff, sbase, stride, T, key, rmax,
+                                       [](const uint32_t (&)[PPL]) { return false; });
 }
 
 // The two partners of a lane in one step of a butterfly over the wavefront
@@ -1067,20 +1079,33 @@ __device__ __forceinline__ void neighbour_event(const DevCam& c, __amdgpu_buffer
   }
 }
 
+// D = 256*S - w*P from the packed key.
+template <int W>
+__device__ __forceinline__ int32_t key_to_d(uint32_t key, int32_t P) {
+  return (int32_t)(key & 0xFFFFFF00u) - W * P;
+}
+
 // Upper bounds for the neighbour peak: the sliding window's key on the high
 // gain of every pixel group, and its low-gain bits.  With 8 pixels per lane in
 // chunks of 8: chunks of 16 need 190 registers, or 316 bytes of scratch (8000
 // events of the 1:3:6 mix 1172 us, 596 with chunks of 8).
-template <int PPL, int W, int CH, int NT, class Fn>
-__device__ __forceinline__ void bound_event(const DevCam& c, __amdgpu_buffer_rsrc_t r, Fn&& fn) {
+//
+// Where the night sky brings many pixels to the boundary level, the windows would
+// cost more than a scan of every pixel, and the bounds would have read the trace
+// for nothing.  Two pixels per lane of the first pass tell so after one chunk
+// (the share of them with a window at the boundary level against c.nbr_noise), if
+// LOOK: false is returned, with fn not called for any group.
+template <int PPL, int W, int CH, int NT, bool LOOK, class Fn>
+__device__ __forceinline__ bool bound_event(const DevCam& c, __amdgpu_buffer_rsrc_t r, uint32_t* seen, Fn&& fn) {
+  constexpr int MAXP = (kMaxPix + NT * PPL - 1) / (NT * PPL), BCH = PPL == 8 ? 8 : CH;
   const int N = c.n_pix, np = c.n_pix_pad, T = c.n_samp;
-  const int npass = (N + NT * PPL - 1) / (NT * PPL);
-  for (int ps = 0; ps < npass; ++ps) {
+  auto pass = [&](int ps, auto&& stop) {
     const int pix0 = (ps * NT + (int)threadIdx.x) * PPL;
     uint32_t key[PPL], rmax[PPL / 2];
 #pragma unroll
     for (int h = 0; h < PPL / 2; ++h) rmax[h] = 0;
-    window_argmax<PPL, W, PPL == 8 ? 8 : CH, true>(r, (uint32_t)pix0 * 2u, 0u, (uint32_t)np * 2u, T, key, rmax);
+    if (!window_argmax<PPL, W, BCH, true>(r, (uint32_t)pix0 * 2u, 0u, (uint32_t)np * 2u, T, key, rmax, stop))
+      return false;
     uint32_t sw = 0;
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
@@ -1088,7 +1113,30 @@ __device__ __forceinline__ void bound_event(const DevCam& c, __amdgpu_buffer_rsr
       if (c.n_gain == 2 && (int)m >= c.hg_switch) sw |= 1u << p;
     }
     fn(pix0, key, sw);
+    return true;
+  };
+  const bool all = pass(0, [&](const uint32_t (&k)[PPL]) {
+    if constexpr (!LOOK) return false;
+    const int pix0 = (int)threadIdx.x * PPL, q0 = pix0 < N ? pix0 : 0;
+    const int2 P = *reinterpret_cast<const int2*>(c.P256 + q0);
+    const int2 Tb = *reinterpret_cast<const int2*>(c.thr_bnd + q0);
+    const uint64_t in0 = __ballot(pix0 < N), in1 = __ballot(pix0 + 1 < N);
+    const uint64_t at0 = __ballot(key_to_d<W>(k[0], P.x) >= Tb.x), at1 = __ballot(key_to_d<W>(k[1], P.y) >= Tb.y);
+    if ((threadIdx.x & (kWave - 1)) == 0)
+      seen[threadIdx.x / kWave] =
+          (uint32_t)(__popcll(in0 & at0) + __popcll(in1 & at1)) | (uint32_t)(__popcll(in0) + __popcll(in1)) << 16;
+    __syncthreads();
+    uint32_t n = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) n += seen[w];
+    return (float)(n & 0xffffu) > nbr_share(c.nbr_noise, BCH) * (float)(n >> 16);
+  });
+  if (!all) return false;
+  if constexpr (MAXP > 1) {
+    const int npass = (N + NT * PPL - 1) / (NT * PPL);
+    for (int ps = 1; ps < npass; ++ps) pass(ps, [](const uint32_t (&)[PPL]) { return false; });
   }
+  return true;
 }
 
 // Keys of every pixel of one event, group by group: fn(pix0, key, sw) for
@@ -1143,12 +1191,6 @@ __device__ __forceinline__ void extract_event(const DevCam& c, __amdgpu_buffer_r
       }
     }
   }
-}
-
-// D = 256*S - w*P from the packed key.
-template <int W>
-__device__ __forceinline__ int32_t key_to_d(uint32_t key, int32_t P) {
-  return (int32_t)(key & 0xFFFFFF00u) - W * P;
 }
 
 // Time numerator Nt = sum_k k*(256*x[s+k] - P) and the in-window peak index
@@ -1234,6 +1276,7 @@ struct NbrSmem {
   TelSmem tel;
   alignas(16) uint16_t xrow[kXrow];
   uint16_t px[kMaxPix];  // pixels whose traces are staged
+  uint32_t seen[16];     // per wavefront: probed pixels << 16 | those at the boundary level
 };
 template <int EX>
 constexpr size_t smem_bytes() {
@@ -1354,10 +1397,11 @@ __device__ __forceinline__ void store_flags(uint8_t* dst, uint64_t fl) {
 // returned.  A group's keys and flags are stored whole: the padding pixels
 // of the last group get flags 0 (their thresholds are the largest int32).
 // BOUND: the windows are upper bounds of the pixels' sums, and a low-gain
-// pixel, whose sum they do not bound, counts as at both thresholds.
-template <int EX, int PPL, int W, int CH, int NT, bool BOUND>
+// pixel, whose sum they do not bound, counts as at both thresholds; -1 in every
+// wavefront if they are given up.
+template <int EX, int PPL, int W, int CH, int NT, bool BOUND, bool LOOK = false>
 __device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __restrict__ ev, TelSmem& sm,
-                                             uint16_t* xrow) {
+                                             uint16_t* xrow, uint32_t* seen = nullptr) {
   static_assert(kRunWave == kWave && kMaxPix % run_length(kMaxPix, NT, PPL) == 0, "whole runs fill the list");
   const int N = c.n_pix, np = c.n_pix_pad;
   const int wave = threadIdx.x / kWave;
@@ -1393,9 +1437,9 @@ __device__ __forceinline__ int extract_phase(const DevCam& c, const uint16_t* __
       store_flags<PPL>(sm.flag + pix0, fl);
     }
   };
-  if constexpr (BOUND)
-    bound_event<PPL, W, CH, NT>(c, r, take);
-  else
+  if constexpr (BOUND) {
+    if (!bound_event<PPL, W, CH, NT, LOOK>(c, r, seen, take)) return -1;
+  } else
     extract_event<EX, PPL, W, CH, NT, true>(c, r, ev, sm.rows, &sm.start, xrow, sm.flag, take);
   if ((threadIdx.x & (kWave - 1)) == 0) sm.nlow_w[wave] = nlow;
   return ncand;
@@ -1957,9 +2001,9 @@ __device__ __forceinline__ rta_hillas_rec given_image(const DevCam& c, TelSmem& 
 // events of the 1:3:6 mix: 1123 us with the full scan of every pixel (six
 // 8-byte LDS reads and some 50 vector instructions per pixel and four
 // slices), 600 us so, at 6.4 TB/s for the trace once and the asked pixels'
-// cache lines a second time (1.35 times the trace in all).  Returns false if more than kNbrAsk pixels are asked or more than kNbrStage traces
-// needed: every pixel is then scanned, from the start.  none: set when no
-// pixel is asked.
+// cache lines a second time (1.35 times the trace in all).  Returns false if
+// more than c.nbr_most traces are needed, or more than fit: every pixel is then
+// scanned, from the start.  none: set when no pixel is asked.
 template <int PPL, int NT, int W>
 __device__ __forceinline__ bool nbr_windows(const DevCam& c, NbrSmem& nm, int ncand, const uint16_t* __restrict__ ev,
                                             bool* none) {
@@ -1996,7 +2040,7 @@ __device__ __forceinline__ bool nbr_windows(const DevCam& c, NbrSmem& nm, int nc
   const int abase = scan_phase(c.n_pix, sm, &n);
   *none = n == 0;
   if (n == 0) return true;
-  if (n > kNbrAsk) return false;
+  if (n > min(c.nbr_most, kNbrAsk)) return false;
   list_mask(abase, sm.ask);
   for (int b = lane; b < ncand; b += kWave) {
     const int i = cand[b];
@@ -2013,7 +2057,7 @@ __device__ __forceinline__ bool nbr_windows(const DevCam& c, NbrSmem& nm, int nc
   __syncthreads();
   int nu;
   const int ubase = scan_phase(c.n_pix, sm, &nu);
-  if (nu > kNbrStage) return false;
+  if (nu > min(c.nbr_most, kNbrStage)) return false;
   list_mask(ubase, nm.px);
   // Tc slices at once, rows of rw dwords (2 mod 4, so that the lanes of a
   // store spread over the banks), row nu all zero for missing neighbours
@@ -2116,17 +2160,21 @@ __device__ __forceinline__ bool nbr_windows(const DevCam& c, NbrSmem& nm, int nc
 // Calibration -> cleaning -> Hillas of one camera event; the threads of
 // wavefront 0 return the record.
 template <int EX, int PPL, int W, int CH, int NT>
-__device__ __forceinline__ rta_hillas_rec process_telescope(const DevCam& c, const uint16_t* __restrict__ ev,
+__device__ __forceinline__ rta_hillas_rec process_telescope(const DevCam& c, const uint16_t* __restrict__ ev, bool look,
                                                             uint8_t* raw) {
   TelSmem& sm = *reinterpret_cast<TelSmem*>(raw);
   uint16_t* xrow = nullptr;
   if constexpr (EX == kExNeighbour) {
     NbrSmem& nm = *reinterpret_cast<NbrSmem*>(raw);
     xrow = nm.xrow;
-    if (!c.nbr_scan) {
-      const int ncand = extract_phase<EX, PPL, W, CH, NT, true>(c, ev, sm, xrow);
+    if (c.nbr_most > 0) {
+      int ncand;
+      if (look && c.nbr_noise < 1.f)
+        ncand = extract_phase<EX, PPL, W, CH, NT, true, true>(c, ev, sm, xrow, nm.seen);
+      else
+        ncand = extract_phase<EX, PPL, W, CH, NT, true>(c, ev, sm, xrow);
       bool none;
-      if (nbr_windows<PPL, NT, W>(c, nm, ncand, ev, &none)) {
+      if (ncand >= 0 && nbr_windows<PPL, NT, W>(c, nm, ncand, ev, &none)) {
         if (none) return empty_image(total_count<NT>(sm));
         return fused_image<PPL, NT, W>(c, sm, ncand, ev);
       }
@@ -2148,14 +2196,14 @@ __device__ __forceinline__ void bad_record(rta_hillas_rec* out) {
 
 // Waves per SIMD the register allocation must leave room for: the neighbour
 // peak's 256-thread workgroups fit four to a compute unit by their LDS (37
-// KB), if the registers allow it; its full scan, bound by latency, loses 8 %
-// with three.  The sliding window keeps two: with 8 pixels per lane, chunks
+// KB), if the registers allow it (512-thread ones two); its full scan, bound by
+// latency, loses 8 % with three.  The sliding window keeps two: with 8 pixels per lane, chunks
 // of 16 and 4 wavefronts the compiler's own choice is 260 registers, one wave
 // (8000 events of the 1:3:6 mix 600 us, 457 with two).  Elsewhere that choice
 // stands.
-template <int EX, int NT>
+template <int EX>
 constexpr int min_waves() {
-  return EX == kExNeighbour && NT == 256 ? 4 : EX == kExSliding ? 2 : 1;
+  return EX == kExNeighbour ? 4 : EX == kExSliding ? 2 : 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -2385,7 +2433,8 @@ __device__ __forceinline__ void fused_telescope(const FusedArgs& a, long long te
     }
     return;
   }
-  rta_hillas_rec r = process_telescope<EX, PPL, W, CH, NT>(a.cams[ty], uniform_ptr(a.traces + off), raw);
+  rta_hillas_rec r = process_telescope<EX, PPL, W, CH, NT>(a.cams[ty], uniform_ptr(a.traces + off), a.nbr_look != 0,
+                                                           raw);
   if (a.classify && threadIdx.x < kWave) classify_telescope(a, tel, r);
   if (threadIdx.x == 0) a.out[tel] = r;
 }
@@ -2413,7 +2462,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // workgroup scheduler (no loop-carried state, so no register pressure from
 // values hoisted across telescopes).
 template <int EX, int PPL, int W, int CH, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(min_waves<EX, NT>()))) void k_fused_grid(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(min_waves<EX>()))) void k_fused_grid(
     FusedArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t raw[smem_bytes<EX>()];
   fused_telescope<EX, PPL, W, CH, NT>(a, (long long)blockIdx.x, raw);

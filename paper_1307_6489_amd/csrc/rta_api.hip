@@ -13,6 +13,7 @@
 
 #include "lattice.h"
 #include "mlp_launch.h"
+#include "nbr_rule.h"
 #include "rta_internal.h"
 
 struct rta_camera {
@@ -191,7 +192,7 @@ rta_status launch_batch(const rta_pipeline* pipe, const rta_batch* b, rta_hillas
   fa.n_types = (int32_t)pipe->cams.size();
   fa.window = pipe->window;
   fa.extractor = pipe->params.extractor;
-  fa.pad_ = 0;
+  fa.nbr_look = b->n_tel > rta::kNbrLookTels * (int64_t)pipe->n_cu ? 1 : 0;
   fa.traces = b->traces;
   fa.traces_len = b->traces_len;
   fa.tel_type = b->tel_type;
@@ -468,11 +469,9 @@ rta_status rta_camera_create(const rta_camera_desc* d, rta_camera** out) {
   c.crc_tab = reinterpret_cast<const uint16_t*>(base + oC);
   c.lat = reinterpret_cast<const int16_t*>(base + oL);
   c.lpos = reinterpret_cast<const uint16_t*>(base + oLP);
-  // Levels within the night-sky noise ask for the windows of most pixels.
-  // 3000 events of 2048 x 128 at 0.1 p.e. per sample: windows of the asked
-  // pixels 340 us at picture / boundary levels of 10 / 5 p.e., 400 at 6 / 3,
-  // 553 at 5 / 2.5, 691 at 4.5 / 3, 818 at 4 / 2; full scan 602 to 616.
-  c.nbr_scan = d->t_pic < 5.f ? 1 : 0;
+  const rta::NbrRule nbr = rta::nbr_rule(N, T, d->t_pic, d->t_bnd);
+  c.nbr_most = nbr.most;
+  c.nbr_noise = nbr.noise;
   cam->health_acc = reinterpret_cast<uint64_t*>(base + oH);
   cam->health_part = reinterpret_cast<uint64_t*>(base + oHP);
   cam->info = rta_camera_info{N, Np, T, G, w, d->fixed_start, c.event_elems};

@@ -36,7 +36,8 @@ struct DevCam {
   // lpos[j] = the position of pixel j (j itself for padding pixels).
   const int16_t* lat;      // [Npad][8]
   const uint16_t* lpos;    // [Npad]
-  int32_t nbr_scan;        // 1: the neighbour peak scans every pixel (picture level within the noise)
+  int32_t nbr_most;        // neighbour peak: most traces that the windows of asked pixels stage (0: all pixels scanned)
+  float nbr_noise;         // neighbour peak: rate of windows at the boundary level that asks for more (1: none)
   // Packet CRC constants of this type (multiplications modulo the CRC
   // polynomial): [0, 256) i*K and [256, 512) i*x^8*K with K = x^(16N), the
   // per-lane finishing factors x^(8 a_l) at [512, 768), then x^(8*body) and
@@ -88,7 +89,7 @@ struct FusedArgs {
   int32_t n_types;
   int32_t window;
   int32_t extractor;       // RTA_EXTRACT_*
-  int32_t pad_;
+  int32_t nbr_look;        // neighbour peak: bounds may be given up after one chunk
   const uint16_t* traces;
   int64_t traces_len;
   const int32_t* tel_type;
