@@ -228,6 +228,15 @@ def _stream(stream=None):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _host(t, stream=None):
+    """``t`` as a numpy array, read behind the work of the call's stream."""
+    import torch
+    if stream is None:
+        return t.cpu().numpy()
+    with torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream, t.device)):
+        return t.cpu().numpy()
+
+
 def _require(t, dtype, shape=None, name="tensor"):
     import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
@@ -611,8 +620,8 @@ def health(cam: Camera, traces, rms_dead=0.5, noisy_factor=3.0, ped_tol=20.0, sa
     _check(lib().rta_health(cam.handle, _ptr(traces), E, ctypes.byref(p), _ptr(pix), _ptr(out), _stream(stream)))
     if not to_host:
         return pix, out
-    pr = pix.cpu().numpy().view(PIXEL_HEALTH_DTYPE).reshape(cam.n_gain, cam.n_pix)
-    cr = out.cpu().numpy().view(CAMERA_HEALTH_DTYPE)[0]
+    pr = _host(pix, stream).view(PIXEL_HEALTH_DTYPE).reshape(cam.n_gain, cam.n_pix)
+    cr = _host(out, stream).view(CAMERA_HEALTH_DTYPE)[0]
     return pr, cr
 
 
@@ -668,7 +677,7 @@ class Sam:
         buf = torch.empty((max(max_alerts, 0) + 1, 4), dtype=torch.float64, device=dev)
         _check(lib().rta_sam_search(self.handle, int(end_bin), _ptr(sig), _ptr(non), _ptr(noff), _ptr(buf[1:]),
                                     int(max_alerts), _ptr(buf), _stream(stream)))
-        host = buf.cpu().numpy()
+        host = _host(buf, stream)
         n = int(host[0].view(np.int32)[0])
         a = host[1:].reshape(-1).view(SAM_ALERT_DTYPE)[:min(n, max_alerts)]
         a = a[np.lexsort((a["ix"], a["iy"], a["scale"]))]
@@ -759,7 +768,7 @@ class Mlp:
         rows = 16 if which in (0, 7) else 64
         out = torch.empty((rows, B), dtype=torch.int16, device="cuda")
         _check(lib().rta_mlp_stored(self.handle, which, B, _ptr(out), _stream(stream)))
-        bits = out.cpu().numpy().view(np.uint16).astype(np.uint32) << 16
+        bits = _host(out, stream).view(np.uint16).astype(np.uint32) << 16
         return bits.view(np.float32)
 
     def train_step(self, x, label, log10e, loss_out=None, stream=None, rows=None):
