@@ -294,16 +294,15 @@ __global__ __launch_bounds__(256) void k_mlp_adam(MlpDev w, int update, float lr
 }  // namespace
 
 hipError_t launch_mlp_rows(const MlpDev& w, const float* x, const float* label, const float* log10e, int B, int Bpad,
-                           float* out, bool train, hipStream_t st) {
-  return launch_mlp_rows_gather(w, x, label, log10e, nullptr, 0, B, Bpad, out, train, st);
+                           int n_cu, float* out, bool train, hipStream_t st) {
+  return launch_mlp_rows_gather(w, x, label, log10e, nullptr, 0, B, Bpad, n_cu, out, train, st);
 }
 
 hipError_t launch_mlp_rows_gather(const MlpDev& w, const float* x, const float* label, const float* log10e,
-                                  const int64_t* rows, int64_t n_data, int B, int Bpad, float* out, bool train,
-                                  hipStream_t st) {
-  // forward: three wavefronts per SIMD of 256 compute units, as the registers
-  // allow, then tiles in turn
-  const int grid = train || Bpad / 16 < 12 * 256 ? Bpad / 16 : 12 * 256;
+                                  const int64_t* rows, int64_t n_data, int B, int Bpad, int n_cu, float* out,
+                                  bool train, hipStream_t st) {
+  // forward: three wavefronts per SIMD, as the registers allow, then tiles in turn
+  const int grid = train || Bpad / 16 < 12 * n_cu ? Bpad / 16 : 12 * n_cu;
   if (train)
     hipLaunchKernelGGL(k_mlp_rows<true>, dim3(grid), dim3(kRowsNT), 0, st, w, x, label, log10e, rows, n_data, B,
                        Bpad, out);

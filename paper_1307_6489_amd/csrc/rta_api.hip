@@ -1225,7 +1225,8 @@ rta_status rta_mlp_forward(rta_mlp* m, const float* x, int64_t B, float* out, rt
   if (B == 0) return RTA_OK;
   if (!x || !out) return fail(RTA_E_INVALID_ARG, "null input or output");
   const int Bpad = (int)((B + 63) & ~63LL);
-  RTA_HIP(rta::launch_mlp_rows(m->dev, x, nullptr, nullptr, (int)B, Bpad, out, false, (hipStream_t)stream));
+  RTA_HIP(rta::launch_mlp_rows(m->dev, x, nullptr, nullptr, (int)B, Bpad, m->n_cu, out, false,
+                               (hipStream_t)stream));
   return RTA_OK;
 }
 
@@ -1236,7 +1237,8 @@ static rta_status mlp_loss_grad(rta_mlp* m, const float* x, const float* label, 
   if (B < 1 || B > m->max_batch) return fail(RTA_E_SHAPE, "batch must be in [1, max_batch]");
   if (!x || !label || !log10e) return fail(RTA_E_INVALID_ARG, "null input");
   const int Bpad = (int)((B + 63) & ~63LL);
-  RTA_HIP(rta::launch_mlp_rows_gather(m->dev, x, label, log10e, rows, n_data, (int)B, Bpad, nullptr, true, st));
+  RTA_HIP(rta::launch_mlp_rows_gather(m->dev, x, label, log10e, rows, n_data, (int)B, Bpad, m->n_cu, nullptr, true,
+                                      st));
   RTA_HIP(rta::launch_mlp_grad(m->dev, (int)B, Bpad, loss, st));
   m->last_B = B;
   return RTA_OK;

@@ -160,7 +160,7 @@ struct EventArgs {
 };
 
 hipError_t launch_mlp_rows(const MlpDev& w, const float* x, const float* label, const float* log10e, int B, int Bpad,
-                           float* out, bool train, hipStream_t st);
+                           int n_cu, float* out, bool train, hipStream_t st);
 hipError_t launch_mlp_grad(const MlpDev& w, int B, int Bpad, float* loss_out, hipStream_t st);
 hipError_t launch_mlp_grad_sum(const MlpDev& w, hipStream_t st);
 hipError_t launch_mlp_adam(const MlpDev& w, bool update, float lr, float b1, float b2, float eps, float c1, float c2,
