@@ -195,19 +195,6 @@ __device__ __forceinline__ f32x4 mlp_forward_tile(const MlpDev& w, bf16x4 xin, b
   return out;
 }
 
-// Standardised input tile of rows r0..r0+15 (row-major raw features [B][10]).
-__device__ __forceinline__ bf16x4 mlp_input_tile(const MlpDev& w, const float* x, int B, int r0) {
-  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-  const int b = r0 + col;
-  float v[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int f = 4 * grp + j;
-    v[j] = (b < B && f < kIn) ? (x[(size_t)b * kIn + f] - w.mean[f]) / w.stdv[f] : 0.f;
-  }
-  return pack4(v[0], v[1], v[2], v[3]);
-}
-
 // The 10 network inputs of a Hillas record.
 __device__ __forceinline__ float record_feature(const rta_hillas_rec& r, int f) {
   switch (f) {

@@ -969,7 +969,6 @@ rta_status rta_sam_create(const rta_sam_params* p, rta_sam** out) {
   d.cell = p->cell;
   d.gamma_cut = p->gamma_cut;
   d.sigma_alert = p->sigma_alert;
-  d.r_on2 = (float)on2;
   d.reach = widest;
   d.n_disc = n_disc;
   for (int k = 0; k < RTA_SAM_MAX_SCALES; ++k) d.scales[k] = k < p->n_scales ? p->scales[k] : 1;

@@ -127,7 +127,7 @@ struct DecodeArgs {
 struct SamDev {
   int32_t grid, n_bins, n_scales, n_offs;
   double t0, bin_s;
-  float cell, gamma_cut, sigma_alert, r_on2;
+  float cell, gamma_cut, sigma_alert;
   int32_t reach;        // largest offset in x or y
   int32_t n_disc;       // offsets of the disc, ahead of the ring's
   int32_t scales[RTA_SAM_MAX_SCALES];
