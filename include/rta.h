@@ -244,8 +244,8 @@ rta_status rta_device_stamp(uint64_t* slot, rta_stream stream);
 /* Create / destroy a camera type.  Quantises pedestals to Q8 and builds the
  * integer cleaning thresholds and neighbour tables on the current device.
  * The camera's device memory also holds the health monitor's scratch:
- * 512 partial blocks of 3 * n_gain * n_pix_pad 64-bit sums (50 MB for a
- * 2048-pixel dual-gain type). */
+ * 256 / n_gain partial blocks of 3 * n_gain * n_pix_pad 64-bit sums (12.6 MB
+ * for a 2048-pixel type). */
 rta_status rta_camera_create(const rta_camera_desc* desc, rta_camera** out);
 rta_status rta_camera_destroy(rta_camera* cam);
 rta_status rta_camera_get_info(const rta_camera* cam, rta_camera_info* info);

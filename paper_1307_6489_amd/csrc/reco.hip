@@ -33,7 +33,7 @@
 // the latencies of steps 2 to 5, and the rate is the telescopes in flight
 // over that chain.  Both were worked on together: the chain after the
 // extraction went from 11 to 5 us, the LDS of a telescope from 32.3 to 16.8
-// KB and the fixed window's registers from 72 to 62 (eight workgroups per
+// KB and the fixed window's registers from 72 to 60 (eight workgroups per
 // compute unit, five before).  8000 camera events of the 1:3:6 mix: fixed
 // window 134 -> 61 us.
 #include <cfloat>
@@ -1233,10 +1233,11 @@ __device__ __forceinline__ uint32_t pixel_flag_at(const DevCam& c, int g, int i,
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup-shared state of one camera event: 16.5 KB, so that LDS lets nine
-// 256-thread workgroups share a compute unit (it was 32.3 KB, five, while
-// every mask pixel had its packed charge and time here; the fixed window,
-// bound by how many telescopes are in flight, runs by it).
+// Workgroup-shared state of one camera event: 16.5 KB, so that LDS has room for
+// nine 256-thread workgroups on a compute unit, one more than its wavefronts
+// allow (it was 32.3 KB, five, while every mask pixel had its packed charge and
+// time here; the fixed window, bound by how many telescopes are in flight, runs
+// by it).
 // ---------------------------------------------------------------------------
 // One mask pixel of a small image, as the lane that found it leaves it for
 // wavefront 0.
@@ -2000,8 +2001,8 @@ __device__ __forceinline__ rta_hillas_rec given_image(const DevCam& c, TelSmem& 
 // lane has an asked pixel, each wavefront a part of the windows.  8000
 // events of the 1:3:6 mix: 1123 us with the full scan of every pixel (six
 // 8-byte LDS reads and some 50 vector instructions per pixel and four
-// slices), 600 us so, at 6.4 TB/s for the trace once and the asked pixels'
-// cache lines a second time (1.35 times the trace in all).  Returns false if
+// slices), 592 us so, at 6.5 TB/s for the trace once and the asked pixels'
+// cache lines a second time (3.84 GB fetched for 2.85 GB of trace).  Returns false if
 // more than c.nbr_most traces are needed, or more than fit: every pixel is then
 // scanned, from the start.  none: set when no pixel is asked.
 template <int PPL, int NT, int W>
@@ -2945,7 +2946,7 @@ hipError_t launch_event(const EventArgs& a, int n_cu, hipStream_t st) {
   const unsigned grid = (unsigned)((a.n_evt + per - 1) / per);
   if (!(a.have_box && a.have_mlp && !a.tel_class))
     hipLaunchKernelGGL(k_event, dim3(grid), dim3(kEvtNT), 0, st, a);
-  else if (a.n_evt <= 2 * (int64_t)n_cu)  // resident at once: two workgroups of 190 registers fit a compute unit
+  else if (a.n_evt <= 2 * (int64_t)n_cu)  // resident at once: two workgroups of 184 registers fit a compute unit
     hipLaunchKernelGGL(k_event_split, dim3((unsigned)a.n_evt), dim3(kEvtNT), 0, st, a);
   else
     hipLaunchKernelGGL(k_event_stream, dim3(grid < 2u * n_cu ? grid : 2u * n_cu), dim3(kEvtNT), 0, st, a);

@@ -179,7 +179,8 @@ hipError_t launch_hillas(const DevCam& c, const float* q, const int32_t* D, cons
                          const uint8_t* gain, int64_t n_evt, rta_hillas_rec* out, hipStream_t st);
 hipError_t launch_decode(const DecodeArgs& a, int n_cu, hipStream_t st);
 // Health accumulation: at most kHealthParts workgroups, each leaving its
-// per-pixel sums in a partial block [3][G][Npad] of the camera's scratch.
+// per-pixel sums of one gain in a partial block of the camera's scratch, [3][G][Npad]
+// for every kHealthParts / G workgroups per gain.
 constexpr int kHealthParts = 256;
 hipError_t launch_health(const DevCam& c, const uint16_t* traces, int64_t n_evt, const rta_health_params& p,
                          uint64_t* part, uint64_t* acc, rta_pixel_health* pix, rta_camera_health* out,
