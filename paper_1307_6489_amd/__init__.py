@@ -233,7 +233,10 @@ def _host(t, stream=None):
     import torch
     if stream is None:
         return t.cpu().numpy()
-    with torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream, t.device)):
+    if not isinstance(stream, torch.cuda.Stream):  # any object with a stream pointer
+        p = stream.cuda_stream
+        stream = torch.cuda.ExternalStream(p, t.device) if p else torch.cuda.default_stream(t.device)
+    with torch.cuda.stream(stream):
         return t.cpu().numpy()
 
 

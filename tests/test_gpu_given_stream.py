@@ -45,6 +45,31 @@ def test_alert_search(torch_dev):
         del keep
 
 
+class Pointer:
+    """A stream known by its pointer alone."""
+
+    def __init__(self, stream):
+        self.cuda_stream = stream.cuda_stream
+
+
+@pytest.mark.parametrize("wrap", [lambda s: s, Pointer])
+def test_health_on_the_default_stream_from_another(torch_dev, wrap):
+    import torch
+    ct = dl0sim.CameraType("default", 61, 16, 1, 28.0)
+    tr = np.random.default_rng(4).integers(280, 330, (40, 1, 16, ct.n_pix_pad)).astype(np.uint16)
+    cam, d = rta.Camera.from_type(ct), to_dev(tr, torch_dev)
+    pix, out = rta.health(cam, d)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for given in (torch.cuda.default_stream(), torch.cuda.Stream()):
+            keep = busy(given, torch_dev)
+            say("health on a busy stream, from another")
+            p2, o2 = rta.health(cam, d, stream=wrap(given))
+            assert np.array_equal(p2, pix) and np.array_equal(o2, out)
+            del keep
+
+
 def test_health(torch_dev):
     import torch
     ct = dl0sim.CameraType("stream", 331, 16, 1, 28.0)
